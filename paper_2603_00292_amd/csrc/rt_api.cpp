@@ -83,19 +83,21 @@ bool valid_variant(const rt_variant& v) {
   return s_ok && wg_ok;
 }
 
+// Grid and ray shares of a traversal launch over n rays.
+struct LaunchShape {
+  uint32_t blocks, share, chunk, tile_shift;  // see TraceParams
+};
+
 // device scratch of one launch: queue counter + global spill stack
 struct Scratch {
-  uint32_t* counter = nullptr;   // [0] ray queue head, [1] overflow ranges
+  uint32_t* counter = nullptr;   // ray queue heads (kRtCounterWords, zero between launches)
   uint32_t* gstack = nullptr;
-  size_t gstack_entries = 0;
-  uint32_t* ranges = nullptr;    // fused finalize: per-wave range lists + overflow list
-  size_t ranges_entries = 0;
+  size_t gstack_words = 0;
 };
 
 void free_scratch(Scratch& s) {
   if (s.counter) (void)hipFree(s.counter);
   if (s.gstack) (void)hipFree(s.gstack);
-  if (s.ranges) (void)hipFree(s.ranges);
   s = Scratch();
 }
 
@@ -105,8 +107,9 @@ struct rt_context_s {
   int device = 0;
   int cu_count = 0;
   rt_variant variant{16, 256};
-  uint32_t refill_min = 32;
-  uint32_t blocks_per_cu = 0;  // 0 = the occupancy API's resident count
+  uint32_t refill_min = 32;    // idle lanes at which a wave takes new rays
+  bool wide_nodes = false;     // RT_WIDE_NODES: 64-bit node addresses whatever the accel's size
+  uint32_t blocks_per_cu = 0;  // RT_BLOCKS_PER_CU; 0 = resident_blocks()
   uint32_t stack_limit = 0;    // RT_STACK_LIMIT: caps every lane's stack below the
                                // accel's bound (exercises the overflow report); 0 = off
   uint32_t* status = nullptr;  // host-mapped word: set by a lane whose stack overflows
@@ -133,6 +136,7 @@ struct rt_accel_s {
   uint32_t root = RT_CHILD_EMPTY;
   uint32_t max_stack = 1;
   float* nodes = nullptr;
+  uint64_t node_bytes = 0;                   // size of nodes
   rt_tri_rec* tris = nullptr;
   rt_inst_rec* insts = nullptr;
   rt_inst_rec64* insts64 = nullptr;
@@ -174,7 +178,7 @@ struct rt_batch_plan_s {
   BatchDesc* descs = nullptr;
   uint32_t* offsets = nullptr;
   Scratch scratch;
-  uint32_t grid = 0;
+  LaunchShape shape{};
   uint32_t workgroup = 256;                  // of `kernel` (the variant at creation)
   uint32_t stack_entries = 16;               // of `kernel`
   const void* kernel = nullptr;
@@ -203,56 +207,77 @@ void destroy_accel(rt_accel_s* a) {
   delete a;
 }
 
-// Resident workgroups of a kernel on the whole device.
+// Workgroups of a traversal kernel that a launch runs at once: those that fit,
+// up to 20 waves per CU.  The kernel is bound by the CU's L1 (a divergent
+// 16-byte load takes it a cycle per lane), and more rays in flight than that
+// crowd it: on 4M incoherent rays 4 / 5 / 6 / 7 workgroups of four waves took
+// 1,449 / 1,424 / 1,473 / 1,557 us, ambient occlusion 1,780 / 1,647 / 1,637 /
+// 1,758 us, 1,024 instances 3,069 / 2,760 / 2,858 / - us.
+constexpr uint32_t kWavesPerCu = 20;
 uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, wg, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 1;
-  return (uint32_t)per_cu * (uint32_t)std::max(cu_count, 1);
+  return std::min((uint32_t)per_cu, kWavesPerCu * 64u / (uint32_t)wg) * (uint32_t)std::max(cu_count, 1);
 }
 
-// Makes sure scratch holds a counter and a spill stack of `entries` entries.
-rt_status ensure_scratch(Scratch& s, size_t entries) {
-  if (!s.counter) RT_HIP(rt_malloc(&s.counter, 256));
-  if (entries > s.gstack_entries) {
+// Makes sure scratch holds zeroed counters and a spill stack of `words` words.
+rt_status ensure_scratch(Scratch& s, size_t words) {
+  if (!s.counter) {
+    uint32_t* c = nullptr;
+    RT_HIP(rt_malloc(&c, kRtCounterWords * sizeof(uint32_t)));
+    hipError_t e = hipMemset(c, 0, kRtCounterWords * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+      (void)hipFree(c);
+      return fail(RT_ERROR_HIP, "zeroing the queue counters: %s", hipGetErrorString(e));
+    }
+    s.counter = c;
+  }
+  if (words > s.gstack_words) {
     if (s.gstack) {
       RT_HIP(hipDeviceSynchronize());
       RT_HIP(hipFree(s.gstack));
       s.gstack = nullptr;
-      s.gstack_entries = 0;
+      s.gstack_words = 0;
     }
-    RT_HIP(rt_malloc(&s.gstack, entries * sizeof(uint32_t)));
-    s.gstack_entries = entries;
+    RT_HIP(rt_malloc(&s.gstack, words * sizeof(uint32_t)));
+    s.gstack_words = words;
   }
   return RT_SUCCESS;
 }
 
-// Range lists of a fused closest-hit launch of `gstride` threads over n rays:
-// kRtRangesPerWave pairs per wave, then the overflow list.  Every range a
-// wave takes holds at least min(refill_min, 64) rays except the one that
-// reaches the end of the queue, so n / min(refill_min, 64) + 1 overflow
-// pairs always suffice.
-rt_status ensure_ranges(Scratch& s, uint32_t gstride, uint32_t n, uint32_t refill_min,
-                        uint32_t** ranges, uint32_t** ovf, uint32_t* ovf_cap) {
-  size_t waves = gstride / 64u;
-  size_t per_wave = 2 * (size_t)kRtRangesPerWave;
-  size_t cap = (size_t)n / std::max<uint32_t>(1u, std::min<uint32_t>(refill_min, 64u)) + 1;
-  size_t entries = waves * per_wave + 2 * cap;
-  if (entries > s.ranges_entries) {
-    if (s.ranges) {
-      RT_HIP(hipDeviceSynchronize());
-      RT_HIP(hipFree(s.ranges));
-      s.ranges = nullptr;
-      s.ranges_entries = 0;
-    }
-    RT_HIP(rt_malloc(&s.ranges, entries * sizeof(uint32_t)));
-    s.ranges_entries = entries;
+// Up to 64 rays per resident wave, every wave takes its rays at once, in one
+// share, and the queues are not used.  Few rays are spread over the chip's
+// 1,024 SIMDs first (64 rays on a 20,480-triangle mesh: 26 us a call with one
+// ray a wave, 35 with 32), then 32 to a wave (65,536 rays: 49 us; 16 to a
+// wave 58).  Beyond, waves take a chunk each and then more from the queues: 64
+// rays, or more when the average wave would need more than a quarter of its
+// kRtRangesPerWave ranges (the waves together can then hold four times the
+// rays, so a wave with a full list always leaves the rest to others).  A queue
+// gets at least 16 tiles, of at most 32,768 rays (tiles of 256 to 65,536 rays
+// are within 3% of each other).
+LaunchShape launch_shape(uint32_t n, uint32_t wg, uint32_t max_blocks) {
+  LaunchShape s;
+  const uint32_t wpb = wg / 64u;
+  const uint64_t waves_max = (uint64_t)max_blocks * wpb;
+  s.tile_shift = 0;
+  if (n <= waves_max * 64u) {
+    const uint32_t spread = std::min(32u, (n + 1023u) / 1024u);
+    s.share = std::max(std::max(1u, spread), (uint32_t)((n + waves_max - 1) / waves_max));
+    s.blocks = std::max(1u, (n + s.share * wpb - 1) / (s.share * wpb));
+    s.chunk = 0;
+  } else {
+    s.blocks = max_blocks;
+    s.chunk = 64;
+    while ((uint64_t)s.chunk * (kRtRangesPerWave / 4u) * waves_max < n) s.chunk *= 2;
+    s.share = s.chunk;
+    while ((1u << s.tile_shift) < s.chunk ||
+           (s.tile_shift < 15u && ((uint64_t)kRtQueues * 16u << (s.tile_shift + 1)) <= n))
+      ++s.tile_shift;
   }
-  *ranges = s.ranges;
-  *ovf = s.ranges + waves * per_wave;
-  *ovf_cap = (uint32_t)cap;
-  return RT_SUCCESS;
+  return s;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -299,6 +324,14 @@ uint32_t* noalloc_ptr(int dev) {
   if (dev < 0 || dev >= kNoAllocMaxDevices) return nullptr;
   std::lock_guard<std::mutex> lk(g_noalloc_mu);
   return g_noalloc_ptr[dev];
+}
+
+// Whether rt_trace_closest_noalloc takes a launch: the array is budgeted for
+// the counters, 256 words per wave and the spill stack of one workgroup, and
+// two words per refill_min rays.
+bool noalloc_accepts(uint32_t n, uint32_t refill_min, const rt_variant& v, uint32_t max_stack) {
+  const size_t spill = max_stack > v.stack_entries ? max_stack - v.stack_entries : 1;
+  return 64 + 2 * ((size_t)n / refill_min + 1) + (v.workgroup / 64u) * 256u + spill * v.workgroup <= kNoAllocWords;
 }
 
 // Reports (and clears) a stack overflow flagged by an earlier traversal on
@@ -372,6 +405,7 @@ rt_status rt_context_create(int hip_device, rt_context* out) {
   c->blocks_per_cu = (uint32_t)std::min(64, std::max(0, env_int("RT_BLOCKS_PER_CU", 0)));
   c->stack_limit = (uint32_t)std::max(0, env_int("RT_STACK_LIMIT", 0));
   c->backward_atomic = env_int("RT_BACKWARD_ATOMIC", 0) != 0;
+  c->wide_nodes = env_int("RT_WIDE_NODES", 0) != 0;
   if (hipEventCreateWithFlags(&c->last_event, hipEventDisableTiming) != hipSuccess) {
     delete c;
     return fail(RT_ERROR_HIP, "rt_context_create: hipEventCreate failed");
@@ -671,6 +705,7 @@ static rt_status build_on_device(rt_context ctx, const rt_mesh_desc& mesh, int w
   a->refit_nodes = o.tri_count ? o.refit_nodes : nullptr;
   a->refit_levels = o.tri_count ? o.refit_levels : std::vector<uint32_t>();
   a->info.node_count = o.tri_count ? o.node_count : 0;
+  a->node_bytes = (uint64_t)a->info.node_count * 32u * (uint32_t)width;
   a->info.triangle_count = o.tri_count;
   a->info.input_triangles = mesh.triangle_count;
   a->info.max_depth = o.tri_count ? o.max_depth : 0;
@@ -864,6 +899,7 @@ static rt_status build_two_level_on_device(rt_context ctx, const rt_mesh_desc* m
     a->root = tlas.root;
     a->max_stack = std::max(tlas.max_stack + 1 + max_blas_stack, 1u);
     a->info.node_count = (uint32_t)node_total;
+    a->node_bytes = node_total * fpn * 4;
     a->info.triangle_count = (uint32_t)tri_total;
     a->info.input_triangles = (uint32_t)std::min<uint64_t>(input_tris, 0xFFFFFFFFull);
     a->info.max_depth = tlas.max_depth + max_blas_depth;
@@ -1042,6 +1078,7 @@ rt_status rt_build(rt_context ctx, const rt_mesh_desc* meshes, uint32_t mesh_cou
     }
     a->max_stack = std::max(a->max_stack, 1u);
     a->info.node_count = (uint32_t)node_total;
+    a->node_bytes = node_total * fpn * 4;
     a->info.triangle_count = (uint32_t)tri_total;
     a->info.input_triangles = (uint32_t)std::min<uint64_t>(input_tris, 0xFFFFFFFFull);
     a->info.max_stack = a->max_stack;
@@ -1184,6 +1221,12 @@ static uint32_t peek_resident(rt_context ctx, const void* kern, int wg) {
   return resident_blocks(kern, wg, ctx->cu_count);
 }
 
+// Stack entries a lane may hold: the accel's bound, which the global stack is
+// sized for, or a lower cap set for the overflow report (at least `entries`).
+static uint32_t stack_cap(rt_context ctx, uint32_t max_stack, uint32_t entries) {
+  return ctx->stack_limit ? std::min(max_stack, std::max(ctx->stack_limit, entries)) : max_stack;
+}
+
 // mode 0: plain query; 2: with query options; 3: all hits (options, lists of
 // `cap` entries and per-ray counts)
 static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit* hits,
@@ -1198,55 +1241,39 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   st = take_overflow(ctx, "trace");
   if (st != RT_SUCCESS) return st;
   rt_variant v = ctx->variant;
-  if (counters || mode >= 2) v = rt_variant{16, 256};
+  const bool wide = !counters && (ctx->wide_nodes || a->node_bytes > 0xFFFFFFFFull);
+  if (counters || mode >= 2 || wide) v = rt_variant{16, 256};
   const void* kern = counters ? rtk_count_kernel(a->width, any, a->two_level)
                               : rtk_trace_kernel(a->width, (int)v.stack_entries, (int)v.workgroup,
-                                                 any, a->two_level, mode);
+                                                 any, a->two_level, mode, wide);
   if (!kern) return fail(RT_ERROR_UNSUPPORTED, "trace: variant not compiled");
   uint32_t wg = v.workgroup;
   uint32_t resident = noalloc ? peek_resident(ctx, kern, (int)wg) : cached_resident(ctx, kern, (int)wg);
-  uint32_t blocks = std::max(std::min<uint32_t>((n + wg - 1) / wg, resident), 1u);
-  size_t spill = a->max_stack > v.stack_entries ? (size_t)(a->max_stack - v.stack_entries) : 1;
+  LaunchShape shape = launch_shape(n, wg, resident);
+  const size_t spill = rtk_spill_words(a->max_stack, v.stack_entries, any, mode);
   const bool fused = !counters && rtk_trace_fuses_finalize(any, a->two_level, mode);
   uint32_t* counter = nullptr;
   uint32_t* gstack = nullptr;
-  uint32_t* ranges = nullptr;
-  uint32_t* ovf = nullptr;
-  uint32_t ovf_cap = 0;
   if (noalloc) {
-    // the fixed array: 64 counter words, then (fused finalize) the per-wave
-    // range lists and the overflow list, then the spill stack; the grid is
-    // narrowed until they fit
+    // the fixed array: the queue counters, then the spill stack; the grid is
+    // narrowed until it fits
     uint32_t* base = noalloc_ptr(a->device);
     if (!base) return fail(RT_ERROR_HIP, "rt_trace_closest_noalloc: no scratch on device %d", a->device);
-    size_t cap_pairs = (size_t)n / std::max<uint32_t>(1u, std::min<uint32_t>(ctx->refill_min, 64u)) + 1;
-    size_t fixed = 64 + (fused ? 2 * cap_pairs : 0);
-    size_t per_block = (fused ? (size_t)(wg / 64u) * 2 * kRtRangesPerWave : 0) + spill * wg;
-    if (fixed + per_block > kNoAllocWords)
+    if (!noalloc_accepts(n, ctx->refill_min, v, a->max_stack) || spill * wg > kNoAllocWords - kRtCounterWords)
       return fail(RT_ERROR_INVALID_VALUE,
                   "rt_trace_closest_noalloc: %u rays with a stack bound of %u need more than the %u-byte "
                   "scratch", n, a->max_stack, (unsigned)RT_NOALLOC_SCRATCH_BYTES);
-    blocks = (uint32_t)std::min<size_t>(blocks, (kNoAllocWords - fixed) / per_block);
+    const uint32_t fit = (uint32_t)std::min<size_t>(resident, (kNoAllocWords - kRtCounterWords) / (spill * wg));
+    if (shape.blocks > fit) shape = launch_shape(n, wg, fit);
     counter = base;
-    if (fused) {
-      ranges = base + 64;
-      ovf = ranges + (size_t)blocks * (wg / 64u) * 2 * kRtRangesPerWave;
-      ovf_cap = (uint32_t)cap_pairs;
-      gstack = ovf + 2 * cap_pairs;
-    } else {
-      gstack = base + 64;
-    }
+    gstack = base + kRtCounterWords;
   } else {
-    st = ensure_scratch(ctx->scratch, spill * (size_t)blocks * wg);
+    st = ensure_scratch(ctx->scratch, spill * (size_t)shape.blocks * wg);
     if (st != RT_SUCCESS) return st;
     counter = ctx->scratch.counter;
     gstack = ctx->scratch.gstack;
-    if (fused) {
-      st = ensure_ranges(ctx->scratch, blocks * wg, n, ctx->refill_min, &ranges, &ovf, &ovf_cap);
-      if (st != RT_SUCCESS) return st;
-    }
   }
-  uint32_t gstride = blocks * wg;
+  const uint32_t blocks = shape.blocks;
   if (ctx->has_last && ctx->last_stream != s) RT_HIP(hipStreamWaitEvent(s, ctx->last_event, 0));
   TraceParams p{};
   p.nodes = a->nodes;
@@ -1259,13 +1286,14 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   p.inst_ids = inst_ids;
   p.occluded = occ;
   p.counter = counter;
+  p.share = shape.share;
+  p.chunk = shape.chunk;
+  p.tile_shift = shape.tile_shift;
   p.gstack = gstack;
   p.root = a->root;
   p.n = n;
-  // the kernels take a bound of at least their LDS entries
-  p.max_stack = ctx->stack_limit ? std::max(std::min(a->max_stack, ctx->stack_limit), v.stack_entries)
-                                 : a->max_stack;
-  p.gstride = gstride;
+  p.max_stack = stack_cap(ctx, a->max_stack, v.stack_entries);
+  p.gstride = blocks * wg;
   p.refill_min = ctx->refill_min;
   p.counters = counters;
   p.phase_counters = (counters && phases) ? 1u : 0u;
@@ -1277,10 +1305,6 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   }
   p.counts = counts;
   p.cap = cap;
-  p.ranges = ranges;
-  p.ovf = ovf;
-  p.ovf_cap = ovf_cap;
-  RT_HIP(rtk_launch_fill(counter, 2, 0u, s));
   size_t tslot = ctx->tbeg.empty() ? 0 : (size_t)(ctx->trecorded % ctx->tbeg.size());
   if (!ctx->tbeg.empty()) RT_HIP(hipEventRecord(ctx->tbeg[tslot], s));
   RT_HIP(rtk_launch_trace(kern, blocks, wg, p, s));
@@ -1290,9 +1314,7 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   }
   if (mode == 3) {
     RT_HIP(rtk_launch_finalize_all(a->two_level, p, s));
-  } else if (fused) {
-    RT_HIP(rtk_launch_finalize_ovf(a->two_level, p, s));
-  } else if (!any) {
+  } else if (!any && !fused) {
     RT_HIP(rtk_launch_finalize(a->two_level, 0, p, s));
   }
   RT_HIP(hipEventRecord(ctx->last_event, s));
@@ -2005,7 +2027,7 @@ static rt_status plan_create(rt_context ctx, const rt_accel* accels, const rt_ra
     off[b + 1] = off[b] + counts[b];
   }
   rt_variant v = ctx->variant;
-  p->kernel = rtk_trace_kernel(width, (int)v.stack_entries, (int)v.workgroup, false, two_level, 1);
+  p->kernel = rtk_trace_kernel(width, (int)v.stack_entries, (int)v.workgroup, false, two_level, 1, true);
   if (!p->kernel) return bail(fail(RT_ERROR_UNSUPPORTED, "rt_batch_plan_create: variant not compiled"));
   uint32_t wg = v.workgroup;
   uint32_t resident;
@@ -2013,15 +2035,15 @@ static rt_status plan_create(rt_context ctx, const rt_accel* accels, const rt_ra
     std::lock_guard<std::mutex> lk(ctx->mu);
     resident = cached_resident(ctx, p->kernel, (int)wg);
   }
-  p->grid = std::max(1u, std::min<uint32_t>((p->total + wg - 1) / wg, resident));
+  p->shape = launch_shape(p->total, wg, resident);
   p->workgroup = wg;
   p->stack_entries = v.stack_entries;
-  size_t spill = max_stack > v.stack_entries ? (size_t)(max_stack - v.stack_entries) : 1;
+  const size_t spill = rtk_spill_words(max_stack, v.stack_entries, false, 1);
   hipError_t e1 = rt_malloc(&p->descs, d.size() * sizeof(BatchDesc));
   hipError_t e2 = rt_malloc(&p->offsets, off.size() * sizeof(uint32_t));
   if (e1 != hipSuccess || e2 != hipSuccess)
     return bail(fail(RT_ERROR_OUT_OF_MEMORY, "rt_batch_plan_create: device allocation failed"));
-  st = ensure_scratch(p->scratch, spill * p->grid * wg);
+  st = ensure_scratch(p->scratch, spill * p->shape.blocks * wg);
   if (st != RT_SUCCESS) return bail(st);
   if (hipMemcpy(p->descs, d.data(), d.size() * sizeof(BatchDesc), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(p->offsets, off.data(), off.size() * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess)
@@ -2047,19 +2069,20 @@ static rt_status enqueue_plan(rt_batch_plan p, hipStream_t s) {
   // creation; a later rt_context_set_variant does not change the plan
   TraceParams q{};
   q.counter = p->scratch.counter;
+  q.share = p->shape.share;
+  q.chunk = p->shape.chunk;
+  q.tile_shift = p->shape.tile_shift;
   q.gstack = p->scratch.gstack;
   q.batches = p->descs;
   q.batch_offsets = p->offsets;
   q.batch_count = p->batch_count;
   q.n = p->total;
-  q.max_stack = p->ctx->stack_limit ? std::max(std::min(p->max_stack, p->ctx->stack_limit), p->stack_entries)
-                                    : p->max_stack;
-  q.gstride = p->grid * p->workgroup;
+  q.max_stack = stack_cap(p->ctx, p->max_stack, p->stack_entries);
+  q.gstride = p->shape.blocks * p->workgroup;
   q.refill_min = p->ctx->refill_min;
   q.status = p->ctx->status;
   q.root = RT_CHILD_EMPTY;
-  RT_HIP(rtk_launch_fill(p->scratch.counter, 1, 0u, s));
-  RT_HIP(rtk_launch_trace(p->kernel, p->grid, p->workgroup, q, s));
+  RT_HIP(rtk_launch_trace(p->kernel, p->shape.blocks, p->workgroup, q, s));
   RT_HIP(rtk_launch_finalize(p->two_level, 1, q, s));
   return RT_SUCCESS;
 }

@@ -32,8 +32,17 @@ struct TraceParams {
   rt_hit* hits;
   uint32_t* inst_ids;
   uint8_t* occluded;
-  uint32_t* counter;     // ray queue head, zero before the launch
-  uint32_t* gstack;      // global stack: (max_stack - S) * gstride entries
+  // Rays are given out in fixed shares of `share` per wave, and beyond those in
+  // chunks.  chunk == 0: the shares cover all rays, the counters are not
+  // touched.  Otherwise tiles of 1 << tile_shift rays are dealt to kRtQueues
+  // queues in turn; the shares of the waves of workgroups q, q + kRtQueues,
+  // ... open queue q, and counter[q * kRtQueueStride] counts the rays of its
+  // chunks given out.  The word after the last queue's counts the workgroups
+  // that are done; the last one zeroes all of them, so they are zero between
+  // launches.
+  uint32_t* counter;
+  uint32_t share, chunk, tile_shift;
+  uint32_t* gstack;      // global stack: per thread of the grid, the entries past the LDS ones
   const BatchDesc* batches;
   const uint32_t* batch_offsets;  // batch_count + 1 prefix sums of counts
   uint32_t batch_count;
@@ -53,19 +62,30 @@ struct TraceParams {
   const uint32_t* skip_prim;
   uint32_t* counts;      // mode 3: hits per ray
   uint32_t cap;          // mode 3: list entries per ray
-  // closest queries on one accel (mode 0): the float64 finalize runs in the
-  // traversal kernel, each wave finalizing the ray
-  // ranges it took from the queue once they are all finished.  ranges: kRtRangesPerWave (first, count) pairs per
-  // wave of the grid; a wave whose list is full appends further ranges to
-  // ovf (ovf_cap pairs, their number in counter[1], zero before the launch),
-  // finalized by a follow-up kernel.
-  uint32_t* ranges;
-  uint32_t* ovf;
-  uint32_t ovf_cap;
 };
 
-// per-wave ray ranges kept for the finalize inside the closest-hit traversal
-constexpr uint32_t kRtRangesPerWave = 128;
+// Closest queries on one accel (mode 0) finalize their hits inside the
+// traversal kernel, each wave the ray ranges it took once they are all
+// finished; a wave remembers at most this many ranges (one per lane) and then
+// takes no more, so the chunks are sized for a quarter of that (launch_shape).
+constexpr uint32_t kRtRangesPerWave = 64;
+
+// Ray queues of a launch (one per die of the chip) and the words between
+// their heads (a cache line each).
+constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
+constexpr uint32_t kRtCounterWords = (kRtQueues + 1) * kRtQueueStride;
+
+// LDS stack entries of a lane in the variant with `stack` entries: 4-byte
+// references for any-hit and all-hit queries; closest hits keep an 8-byte
+// (distance, reference) entry, and 5/8 as many, which holds eight workgroups
+// of 256 threads in a CU's 160 KB.
+constexpr int rtk_lds_entries(int stack, bool cull) { return cull ? stack * 5 / 8 : stack; }
+constexpr bool rtk_stack_culls(bool any, int mode) { return !any && mode != 3; }
+// global stack words per thread (4-byte references) for a bound of max_stack entries
+inline size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode) {
+  const uint32_t lds = (uint32_t)rtk_lds_entries((int)stack, rtk_stack_culls(any, mode));
+  return max_stack > lds ? max_stack - lds : 1u;
+}
 
 // Single-level adjoint (a workgroup of 1024 threads per tile of rta::kTile
 // rays): writes the ray gradients and places each hit ray's record in its
@@ -132,18 +152,17 @@ struct AoParams {
 // Kernel handle for a variant (mode 0: one accel, mode 1: batched closest,
 // mode 2: one accel with query options, mode 3: all hits with query options;
 // modes 2 and 3 exist for stack 16 / workgroup 256 only); nullptr when the
-// combination is not compiled.
-const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode);
+// combination is not compiled.  wide (stack 16 / workgroup 256 only): for
+// accels whose node array does not fit 32-bit byte offsets; batched plans
+// always use 64-bit addresses.
+const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode, bool wide);
 const void* rtk_count_kernel(int width, bool any, bool inst);
 hipError_t rtk_launch_trace(const void* kern, uint32_t grid, uint32_t wg, const TraceParams& p,
                             hipStream_t stream);
 // float64 finalize of closest hits written by a trace launch with the same params
 hipError_t rtk_launch_finalize(bool inst, int mode, const TraceParams& p, hipStream_t stream);
 // true when the traversal kernel of (any, inst, mode) finalizes its own hits
-// (it then needs p.ranges / p.ovf and rtk_launch_finalize_ovf afterwards)
 bool rtk_trace_fuses_finalize(bool any, bool inst, int mode);
-// float64 finalize of the overflow ranges of a fused traversal launch
-hipError_t rtk_launch_finalize_ovf(bool inst, const TraceParams& p, hipStream_t stream);
 // float64 finalize of the hit lists of an all-hits launch (n * cap entries)
 hipError_t rtk_launch_finalize_all(bool inst, const TraceParams& p, hipStream_t stream);
 hipError_t rtk_launch_backward(const BackwardParams& p, hipStream_t stream);
@@ -154,7 +173,6 @@ hipError_t rtk_launch_refit_tris(rt_tri_rec* tris, uint32_t n, const rt_mesh_dev
                                  hipStream_t stream);
 hipError_t rtk_launch_refit_nodes(int width, float* nodes, const rt_tri_rec* tris,
                                   const uint32_t* node_ids, uint32_t count, hipStream_t stream);
-hipError_t rtk_launch_fill(uint32_t* ptr, uint32_t n, uint32_t value, hipStream_t stream);
 hipError_t rtk_launch_ao_rays(const AoParams& p, hipStream_t stream);
 hipError_t rtk_launch_ao_resolve(const uint8_t* occluded, uint32_t n, uint32_t samples, float* ao,
                                  hipStream_t stream);

@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "rt_kernels.h"
 #include "rt_layout.h"
 
@@ -31,13 +33,16 @@ __device__ constexpr float kSlabWiden = 3.5762793e-7f;
 // relative widening of the best distance in the box test, so that a box
 // holding an exact tie in t with a lower id is still visited
 __device__ constexpr float kTieWiden = 9.5367432e-7f;  // 2^-20
+// the same for entries popped off the stack, wide enough for the rounding of
+// a grazing triangle's float32 t
+__device__ constexpr float kPopWiden = 1.52587891e-5f;  // 2^-16
 
 #define RT_STACK_MARKER 0xFFFFFFFEu  // "leave the instance, restore the world ray"
 
 struct RayState {
   float ox, oy, oz, dx, dy, dz;
   float ix, iy, iz;
-  float tmin, tmax;
+  float tmin;
   uint32_t sx, sy, sz;  // 1 when the direction's sign bit is set
 };
 
@@ -68,48 +73,95 @@ __device__ __forceinline__ rt_ray load_ray(const rt_ray* rays, uint32_t i) {
 }
 
 // ---------------------------------------------------------------------------
-// per-lane traversal stack: top S entries in LDS, the rest in global memory
+// per-lane traversal stack: the first D entries in LDS, the rest in global memory
 // ---------------------------------------------------------------------------
-// Entry i of a lane's stack lives in LDS slot (i mod S) while it is one of the
-// S newest entries; older entries live at gstack[(i - S) * gstride + gtid].
+// An entry is a child reference, for closest hits (CULL) with the distance at
+// which the ray enters the child's box: an entry farther than the nearest hit
+// found since it was pushed is dropped when it is popped, without a fetch.
+// Slot 0 of a lane's LDS column holds a sentinel (RT_CHILD_EMPTY at distance
+// -inf), so a pop needs no check for an empty stack.  Entry i lives in LDS
+// slot i + 1 while i < D, and at gstack[(i - D) * gstride + thread] beyond: D
+// covers all but some 0.5% of the pushes of the incoherent workloads.
 // A push beyond `cap` (the builder's bound on the entries a ray can need,
-// which the global stack is sized for; never below S) is not stored.  The
+// which the global stack is sized for; never below D) is not stored.  The
 // counting variant (CHECK) also remembers it and raises the launch's
 // host-mapped status word at the end, which the host turns into an error on
 // the context's next call, and records the deepest fill.  The query kernels
-// do neither: any observable action on that branch (a flag carried through
-// the loop, a store of any kind) measured 1.3% on the closest-hit kernel.
-template <int S, int WG, bool CHECK = false>
+// do neither.
+template <bool CULL>
+using StackEntry = typename std::conditional<CULL, uint64_t, uint32_t>::type;  // CULL: distance << 32 | reference
+
+template <int D, int WG, bool CULL, bool CHECK>
 struct Stack {
-  uint32_t* lds;       // this lane's column: lds[slot * WG]
-  uint32_t* glob;      // this lane's column: glob[i * gstride]
+  using E = StackEntry<CULL>;
+  static constexpr uint32_t kStep = WG * sizeof(E);
+  static constexpr uint32_t kLdsEnd = (D + 1) * kStep;  // a byte offset at or past it is a global entry
+  char* lds;           // the workgroup's array
+  uint32_t* glob;      // this lane's column: glob[i * gstride] (references; a popped one is not culled)
   uint32_t gstride;
-  uint32_t cap;        // total entries this lane may hold (at least S)
-  uint32_t sp;
-  uint32_t peak;       // CHECK: the largest sp reached
+  uint32_t cap;        // entries this lane may hold (at least D)
+  uint32_t off;        // byte offset in lds of the slot the next push takes
+  uint32_t peak;       // CHECK: the most entries held
+  uint32_t spills;     // CHECK: entries stored in global memory
   bool over;           // CHECK: a push was dropped
 
-  __device__ __forceinline__ void push(uint32_t v) {
-    uint32_t slot = sp & (S - 1);
-    if (sp >= S) {
-      // only a stack that spills can reach the bound (cap >= S)
-      if (sp >= cap) {
-        if constexpr (CHECK) over = true;
-        return;
-      }
-      glob[(size_t)(sp - S) * gstride] = lds[slot * WG];
-    }
-    lds[slot * WG] = v;
-    ++sp;
-    if constexpr (CHECK) peak = max(peak, sp);
+  __device__ __forceinline__ void init(uint32_t tid) {
+    off = tid * (uint32_t)sizeof(E);
+    E e = RT_CHILD_EMPTY;
+    if constexpr (CULL) e |= (uint64_t)0xff800000u << 32;
+    *reinterpret_cast<E*>(lds + off) = e;
+    off += kStep;
+    peak = spills = 0;
+    over = false;
   }
-  __device__ __forceinline__ uint32_t pop() {
-    if (sp == 0) return RT_CHILD_EMPTY;
-    --sp;
-    uint32_t slot = sp & (S - 1);
-    uint32_t v = lds[slot * WG];
-    if (sp >= S) lds[slot * WG] = glob[(size_t)(sp - S) * gstride];
-    return v;
+  __device__ __forceinline__ void clear(uint32_t tid) { off = tid * (uint32_t)sizeof(E) + kStep; }
+  __device__ __forceinline__ uint32_t entries() const { return off / kStep - 1u; }
+  // true when `n` pushes all land in LDS
+  __device__ __forceinline__ bool fits(int n) const { return off < kLdsEnd - (uint32_t)min(n - 1, D) * kStep && n - 1 <= D; }
+  __device__ __forceinline__ void push_lds(E e) {
+    *reinterpret_cast<E*>(lds + off) = e;
+    off += kStep;
+    if constexpr (CHECK) peak = max(peak, entries());
+  }
+  __device__ __forceinline__ void push(E e) {
+    if (off < kLdsEnd) {
+      push_lds(e);
+      return;
+    }
+    const uint32_t i = entries();
+    if (i >= cap) {
+      if constexpr (CHECK) over = true;
+      return;
+    }
+    glob[(size_t)(i - D) * gstride] = (uint32_t)e;
+    off += kStep;
+    if constexpr (CHECK) {
+      ++spills;
+      peak = max(peak, i + 1u);
+    }
+  }
+  __device__ __forceinline__ E pop_entry() {
+    off -= kStep;
+    if (off >= kLdsEnd) {
+      E e = glob[(size_t)(entries() - D) * gstride];
+      if constexpr (CULL) e |= (uint64_t)0xff800000u << 32;
+      return e;
+    }
+    return *reinterpret_cast<const E*>(lds + off);
+  }
+  // The next child to visit: the topmost entry not farther than `far` (CULL;
+  // the sentinel when there is none, which leaves the stack empty).
+  __device__ __forceinline__ uint32_t pop(float far, uint32_t tid) {
+    E e;
+    if constexpr (CULL) {
+      do {
+        e = pop_entry();
+      } while (__uint_as_float((uint32_t)(e >> 32)) > far);
+    } else {
+      e = pop_entry();
+    }
+    if ((uint32_t)e == RT_CHILD_EMPTY) clear(tid);
+    return (uint32_t)e;
   }
 };
 
@@ -120,43 +172,68 @@ struct Geo {
   const float* nodes;          // node_count * 8W floats
   const float4* tris;          // 3 float4 per record
   const rt_inst_rec* insts;    // two-level only
-  const rt_inst_rec64* insts64;
-  const rt_mesh_dev* meshes;
   uint32_t root;
-  uint32_t max_stack;
 };
 
-// W-wide node visit: returns the child refs that the ray enters, nearest
-// first, in keys k[0..W-1] (0xFFFFFFFF = no child).
-// DIRECT (4-wide nodes only): each lane loads its near and far plane
-// vectors at lane-dependent addresses (lo or hi by the sign of the ray's
-// direction) instead of loading both and selecting; it needs more registers,
-// which pays only where they are free (the single-level any-hit kernel:
-// +2%; the closest-hit kernel loses a wave per SIMD and 5%).
-template <int W, bool DIRECT = false>
-__device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, const RayState& r,
-                                           float tcull, uint32_t* out_ref, int& n_out) {
-  constexpr int NF4 = (W == 2) ? 4 : (7 * W) / 4;  // skip trailing pad when it fills a float4
-  constexpr bool PRE = DIRECT && W == 4;            // planes loaded in (near, far) order
-  const float4* p = reinterpret_cast<const float4*>(nodes + (size_t)idx * (8 * W));
-  float nd[4 * NF4];
-  if constexpr (PRE) {
-    float4 v[7];
-    v[0] = p[r.sx];
-    v[1] = p[1u - r.sx];
-    v[2] = p[2u + r.sy];
-    v[3] = p[3u - r.sy];
-    v[4] = p[4u + r.sz];
-    v[5] = p[5u - r.sz];
-    v[6] = p[6];
+// Raw 64-bit minimum and maximum: the operands are (distance, reference)
+// pairs with a float32 distance in the upper word, never a NaN pattern as
+// float64 (the float32 exponent reaches 0xFF, the upper 11 bits 0x7F8), so
+// ordering them as float64 orders them by distance, and one instruction moves
+// the reference along with its key.
+__device__ __forceinline__ double raw_min(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double raw_max(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// W-wide node visit: (entry distance, child reference) of the children that
+// the ray enters, nearest first; the others follow with distance +inf.
+// A divergent 16-byte load costs the CU's address unit one cycle per lane, so
+// a 4-wide visit costs 7 cycles per lane there and its box tests about twice
+// that in VALU issue; both are kept low:
+// OFF32 (nodes of one accel in less than 4 GiB): 32-bit byte offsets from the
+// uniform node pointer, and each lane loads its near and far planes at
+// offsets chosen by the sign of its direction instead of loading both in
+// fixed order and selecting (24 selects fewer for W = 4).  2-wide nodes,
+// whose lo and hi planes share a 16-byte load, and per-lane node pointers
+// (batched plans) select after the load.
+template <int W, bool OFF32>
+__device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, const RayState& r, float tcull,
+                                           double (&e)[W]) {
+  constexpr bool DIRECT = OFF32 && W >= 4;
+  float nr[3][W], fr[3][W];
+  uint32_t ref[W];
+  const char* base = reinterpret_cast<const char*>(nodes);
+  if constexpr (DIRECT) {
+    constexpr uint32_t P = 4u * W;  // bytes of one plane array
+    const uint32_t b = idx * (32u * W);
+    const uint32_t s[3] = {r.sx, r.sy, r.sz};
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      nd[4 * i + 0] = v[i].x;
-      nd[4 * i + 1] = v[i].y;
-      nd[4 * i + 2] = v[i].z;
-      nd[4 * i + 3] = v[i].w;
+    for (int a = 0; a < 3; ++a) {
+      const uint32_t n = b | (s[a] * P), f = n ^ P;
+#pragma unroll
+      for (int c = 0; c < W / 4; ++c) {
+        const float4 x = *reinterpret_cast<const float4*>(base + (size_t)n + 2 * a * P + 16 * c);
+        const float4 y = *reinterpret_cast<const float4*>(base + (size_t)f + 2 * a * P + 16 * c);
+        nr[a][4 * c] = x.x; nr[a][4 * c + 1] = x.y; nr[a][4 * c + 2] = x.z; nr[a][4 * c + 3] = x.w;
+        fr[a][4 * c] = y.x; fr[a][4 * c + 1] = y.y; fr[a][4 * c + 2] = y.z; fr[a][4 * c + 3] = y.w;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < W / 4; ++c) {
+      const uint4 x = *reinterpret_cast<const uint4*>(base + (size_t)b + 6 * P + 16 * c);
+      ref[4 * c] = x.x; ref[4 * c + 1] = x.y; ref[4 * c + 2] = x.z; ref[4 * c + 3] = x.w;
     }
   } else {
+    constexpr int NF4 = (W == 2) ? 4 : (7 * W) / 4;  // skip trailing pad when it fills a float4
+    const float4* p = OFF32 ? reinterpret_cast<const float4*>(base + (size_t)(idx * (32u * W)))
+                            : reinterpret_cast<const float4*>(nodes + (size_t)idx * (8 * W));
+    float nd[4 * NF4];
 #pragma unroll
     for (int i = 0; i < NF4; ++i) {
       float4 v = p[i];
@@ -165,20 +242,23 @@ __device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, con
       nd[4 * i + 2] = v.z;
       nd[4 * i + 3] = v.w;
     }
+    const uint32_t s[3] = {r.sx, r.sy, r.sz};
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        const float lo = nd[(2 * a) * W + i], hi = nd[(2 * a + 1) * W + i];
+        nr[a][i] = s[a] ? hi : lo;
+        fr[a][i] = s[a] ? lo : hi;
+      }
+#pragma unroll
+    for (int i = 0; i < W; ++i) ref[i] = __float_as_uint(nd[6 * W + i]);
   }
-  constexpr int SH = (W == 2) ? 1 : ((W == 4) ? 2 : 3);
-  uint32_t key[W];
 #pragma unroll
   for (int i = 0; i < W; ++i) {
-    float lox = nd[0 * W + i], hix = nd[1 * W + i];
-    float loy = nd[2 * W + i], hiy = nd[3 * W + i];
-    float loz = nd[4 * W + i], hiz = nd[5 * W + i];
-    float nx = PRE ? lox : (r.sx ? hix : lox), fx = PRE ? hix : (r.sx ? lox : hix);
-    float ny = PRE ? loy : (r.sy ? hiy : loy), fy = PRE ? hiy : (r.sy ? loy : hiy);
-    float nz = PRE ? loz : (r.sz ? hiz : loz), fz = PRE ? hiz : (r.sz ? loz : hiz);
-    float tnx = (nx - r.ox) * r.ix, tfx = (fx - r.ox) * r.ix;
-    float tny = (ny - r.oy) * r.iy, tfy = (fy - r.oy) * r.iy;
-    float tnz = (nz - r.oz) * r.iz, tfz = (fz - r.oz) * r.iz;
+    float tnx = (nr[0][i] - r.ox) * r.ix, tfx = (fr[0][i] - r.ox) * r.ix;
+    float tny = (nr[1][i] - r.oy) * r.iy, tfy = (fr[1][i] - r.oy) * r.iy;
+    float tnz = (nr[2][i] - r.oz) * r.iz, tfz = (fr[2][i] - r.oz) * r.iz;
     // fmaxf/fminf ignore a NaN operand (0 * inf on a slab boundary with a
     // zero direction component), which is the correct "no constraint".
     float tn = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, r.tmin));
@@ -189,26 +269,14 @@ __device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, con
     // NaN-ignoring fminf and the box kept
     tf = fminf(tf, tcull);
     tf = fmaf(fabsf(tf), kSlabWiden, tf);
-    bool hit = (tn <= tf) & (tn < __int_as_float(0x7f800000));
-    key[i] = hit ? ((__float_as_uint(tn) & ~((1u << SH) - 1u)) | (uint32_t)i) : 0xFFFFFFFFu;
+    const float t = (tn <= tf) ? tn : __int_as_float(0x7f800000);
+    e[i] = __longlong_as_double(((long long)__float_as_uint(t) << 32) | ref[i]);
   }
-  // sort (key, child) pairs by key, nearest first; missed children (key
-  // 0xFFFFFFFF) sort last.  Moving the child reference with its key costs two
-  // selects per exchange and saves looking it up by slot afterwards.
-  uint32_t ref[W];
-#pragma unroll
-  for (int i = 0; i < W; ++i) ref[i] = __float_as_uint(nd[6 * W + i]);
-#define RT_CSWAP(a, b)                                  \
-  {                                                     \
-    bool s_ = key[b] < key[a];                          \
-    uint32_t k0_ = s_ ? key[b] : key[a];                \
-    uint32_t k1_ = s_ ? key[a] : key[b];                \
-    uint32_t r0_ = s_ ? ref[b] : ref[a];                \
-    uint32_t r1_ = s_ ? ref[a] : ref[b];                \
-    key[a] = k0_;                                       \
-    key[b] = k1_;                                       \
-    ref[a] = r0_;                                       \
-    ref[b] = r1_;                                       \
+#define RT_CSWAP(a, b)                    \
+  {                                       \
+    const double lo_ = raw_min(e[a], e[b]); \
+    e[b] = raw_max(e[a], e[b]);           \
+    e[a] = lo_;                           \
   }
   if constexpr (W == 2) {
     RT_CSWAP(0, 1);
@@ -224,12 +292,6 @@ __device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, con
     RT_CSWAP(1, 2); RT_CSWAP(3, 4); RT_CSWAP(5, 6);
   }
 #undef RT_CSWAP
-  n_out = 0;
-#pragma unroll
-  for (int i = 0; i < W; ++i) {
-    out_ref[i] = ref[i];
-    n_out += (key[i] != 0xFFFFFFFFu) ? 1 : 0;
-  }
 }
 
 // Watertight float32 ray/triangle test.  The record's vertices are sorted
@@ -305,35 +367,23 @@ __device__ __forceinline__ bool finalize64(const float4* tris, uint32_t rec, dou
 
 // world -> object ray with the float32 instance map (no renormalisation, so
 // t is shared between the two spaces)
-// (r holds the world ray on entry; tmin and tmax carry over unchanged)
-__device__ __forceinline__ void to_object_od(const rt_inst_rec& I, float wox, float woy, float woz, float wdx,
-                                             float wdy, float wdz, RayState& r) {
+// (r holds the world ray on entry; tmin carries over unchanged)
+__device__ __forceinline__ void to_object(const rt_inst_rec& I, RayState& r) {
+  const float wox = r.ox, woy = r.oy, woz = r.oz, wdx = r.dx, wdy = r.dy, wdz = r.dz;
   r.ox = I.r0[0] * wox + I.r0[1] * woy + I.r0[2] * woz + I.r0[3];
   r.oy = I.r1[0] * wox + I.r1[1] * woy + I.r1[2] * woz + I.r1[3];
   r.oz = I.r2[0] * wox + I.r2[1] * woy + I.r2[2] * woz + I.r2[3];
   r.dx = I.r0[0] * wdx + I.r0[1] * wdy + I.r0[2] * wdz;
   r.dy = I.r1[0] * wdx + I.r1[1] * wdy + I.r1[2] * wdz;
   r.dz = I.r2[0] * wdx + I.r2[1] * wdy + I.r2[2] * wdz;
-}
-
-__device__ __forceinline__ void to_object(const rt_inst_rec& I, RayState& r) {
-  to_object_od(I, r.ox, r.oy, r.oz, r.dx, r.dy, r.dz, r);
   ray_setup(r);
 }
 
 __device__ __forceinline__ void world_state(const rt_ray& w, RayState& r) {
   r.ox = w.ox; r.oy = w.oy; r.oz = w.oz;
   r.dx = w.dx; r.dy = w.dy; r.dz = w.dz;
-  r.tmin = w.tmin; r.tmax = w.tmax;
+  r.tmin = w.tmin;
   ray_setup(r);
-}
-
-__device__ __forceinline__ bool is_internal(uint32_t ref) { return (ref & RT_LEAF_BIT) == 0u; }
-__device__ __forceinline__ bool is_inst(uint32_t ref) {
-  return (ref & (RT_LEAF_BIT | RT_INST_BIT)) == (RT_LEAF_BIT | RT_INST_BIT) && ref != RT_CHILD_EMPTY;
-}
-__device__ __forceinline__ bool is_tri_leaf(uint32_t ref) {
-  return (ref & (RT_LEAF_BIT | RT_INST_BIT)) == RT_LEAF_BIT;
 }
 
 // Inserts the hit (t, inst, prim) into a lane's list of the `cap` nearest
@@ -353,19 +403,6 @@ __device__ __forceinline__ void list_insert(float4* L, uint32_t found, uint32_t 
   if (pos < cap) L[pos] = make_float4(t, __uint_as_float(prim), __uint_as_float(inst), __uint_as_float(rec));
 }
 
-// ---------------------------------------------------------------------------
-// the persistent traversal kernel
-// ---------------------------------------------------------------------------
-// MODE 0: one accel (uniform geometry); MODE 1: batched (geometry per lane
-// from the batch descriptor of the lane's ray); MODE 2: one accel with the
-// query options (ray masks against instance masks, a skipped triangle per
-// ray); MODE 3: as MODE 2, enumerating all hits within [tmin, tmax] (no
-// culling by the nearest hit) into per-ray lists of the `cap` nearest.
-// Two-level kernels of width <= 4 are asked to fit six waves per SIMD (80
-// VGPRs): on the 1,024-instance workload 4 -> 6 waves measured +12%, with no
-// spills (8-wide nodes, the counting variants and the batched mode, which
-// keeps per-lane geometry pointers, would spill, so they keep the compiler's
-// choice).
 // float64 finalize of ray `local`'s closest hit: the traversal left float32
 // t, the winner's triangle record and (two-level) its instance in hits[local];
 // (t, u, v) are recomputed in float64 from the record and the record's prim
@@ -431,405 +468,386 @@ __device__ __forceinline__ void finalize_index(const TraceParams& P, uint32_t i)
   finalize_ray<INST>(rays, hits, tris, insts64, inst_ids, local);
 }
 
-template <int W, bool INST, bool COUNT, int MODE>
-constexpr int trace_min_waves() { return (INST && W <= 4 && !COUNT && MODE != 1) ? 5 : 1; }
-template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool COUNT = false>
-__global__ __launch_bounds__(WG, (trace_min_waves<W, INST, COUNT, MODE>())) void trace_kernel(TraceParams P) {
-  __shared__ uint32_t lds_stack[S * WG];
+// ---------------------------------------------------------------------------
+// the persistent traversal kernel
+// ---------------------------------------------------------------------------
+// MODE 0: one accel (uniform geometry); MODE 1: batched (geometry per lane
+// from the batch descriptor of the lane's ray); MODE 2: one accel with the
+// query options (ray masks against instance masks, a skipped triangle per
+// ray); MODE 3: as MODE 2, enumerating all hits within [tmin, tmax] (no
+// culling by the nearest hit) into per-ray lists of the `cap` nearest.
+//
+// A wave takes one step per pass of its loop: a node visit for every lane
+// whose next child is an internal node, or one triangle test for every lane
+// with a leaf, whichever serves more lanes for its cost (a node visit costs
+// about two triangle tests); two-level accels have a third kind, instance
+// entry and exit.  A lane with a leaf in hand keeps traversing until it meets
+// a second one or a frame change, so it can serve either step.  Running each
+// phase until no lane of the wave had work left in it, as before, left 36% of
+// the lanes busy in node visits and 29% in triangle tests on incoherent rays;
+// choosing step by step leaves about 64% and 31%.
+template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool OFF32, bool COUNT = false>
+__global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
+  constexpr bool CULL = !ANY && MODE != 3;
+  constexpr int D = rtk_lds_entries(S, CULL);
+  using Stk = Stack<D, WG, CULL, COUNT>;
+  using E = typename Stk::E;
+  __shared__ __align__(8) char lds_stack[Stk::kLdsEnd];
   // two-level: the world ray's origin and direction, restored on leaving an
   // instance (kept out of registers)
   __shared__ float lds_world[INST ? 6 * WG : 1];
+  __shared__ uint32_t lds_done, lds_empty;   // waves done; queues found used up (bit mask)
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
   const uint32_t gtid = blockIdx.x * WG + tid;
   // closest queries on one accel finalize their own hits (see TraceParams)
   constexpr bool FUSED = !ANY && MODE == 0 && !COUNT;
-  uint32_t* my_ranges = FUSED ? P.ranges + (size_t)(gtid >> 6) * (2 * kRtRangesPerWave) : nullptr;
-  uint32_t n_ranges = 0;
-  const uint64_t lanemask_lt = (lane == 0) ? 0ull : (~0ull >> (64u - lane));
 
   Geo g;
   g.nodes = P.nodes;
   g.tris = reinterpret_cast<const float4*>(P.tris);
   g.insts = P.insts;
-  g.insts64 = P.insts64;
-  g.meshes = P.meshes;
   g.root = P.root;
-  g.max_stack = P.max_stack;
 
-  Stack<S, WG, COUNT> st;
-  st.lds = lds_stack + tid;
+  Stk st;
+  st.lds = lds_stack;
   st.glob = P.gstack + gtid;
   st.gstride = P.gstride;
   st.cap = P.max_stack;
-  st.sp = 0;
-  st.peak = 0;
-  st.over = false;
+  st.init(tid);
+  if (tid == 0) lds_done = lds_empty = 0;
+  __syncthreads();
 
   RayState r;
-  uint32_t ray_id = 0;
-  uint32_t cur = RT_CHILD_EMPTY;
-  // postponed triangle leaves, oldest first: up to three for closest hits
-  // and six for any-hit on one accel, two on two-level accels (the counts
-  // measured fastest)
-  constexpr int K = INST ? 2 : (ANY ? 6 : 3);
-  uint32_t pq[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) pq[k] = RT_CHILD_EMPTY;
-  float best_t = 0.0f;
+  uint32_t ray_id = RT_INVALID_ID;   // the lane's ray, until its result is stored
+  uint32_t cur = RT_CHILD_EMPTY;     // next child to visit
+  uint32_t leaf = 0;                 // triangles in hand: count << RT_LEAF_COUNT_SHIFT | first record
+  float best_t = 0.0f, tcull = 0.0f;
   // the nearest hit so far: its triangle record (RT_INVALID_ID: none yet;
   // the prim id is read from the record where a tie needs it and by the
   // finalize) and instance
   uint32_t best_rec = RT_INVALID_ID, best_inst = RT_INVALID_ID, cur_inst = 0;
-  // two-level: the instance of each postponed leaf, and whether the
-  // traversal ray is in an instance's object space (cur_inst) or in world
-  // space
-  uint32_t pin[K];
-  bool in_inst = false;
   rt_hit* hit_out = P.hits;
-  uint8_t* occ_out = P.occluded;
-  const rt_ray* ray_in = P.rays;
-  bool live = false, retired = false;
-  uint32_t batch = 0;
   uint32_t rmask = 0xFFFFFFFFu, skip_i = RT_INVALID_ID, skip_p = RT_INVALID_ID, found = 0;
-  uint64_t n_nodes = 0, n_tris = 0, n_spill = 0;
-  // counting variant, wave level: passes of the outer loop, refills, and
-  // iterations of the node and the leaf loops (counted by the wave's first
-  // active lane, so every wave iteration once)
+  // counting variant: lane-level work, and wave-level passes of the outer
+  // loop, refills, node and triangle steps
+  uint64_t n_nodes = 0, n_tris = 0;
   uint64_t w_outer = 0, w_refill = 0, w_node = 0, w_leaf = 0;
-  auto first_active = [&]() -> bool {
-    return lane == (uint32_t)(__ffsll((unsigned long long)__ballot(1)) - 1);
+
+  // The wave's rays: [q_next, q_end), first a fixed share, then chunks of the
+  // queues.  Workgroups go to the chip's eight dies in turn, each with its own
+  // L2, and the rays are dealt to the dies in tiles: a die works through
+  // neighbouring rays (of one mesh in a batched plan, of one part of an
+  // image), and takes chunks of other queues only when its own is used up.
+  // (One queue for all: batched plans 1,180 against 770 us, and adds to one
+  // address complete at only some 75 million a second on this chip.)
+  // Fused finalize: lane k keeps the first ray of the k-th range the wave
+  // took, and a wave with kRtRangesPerWave ranges takes no more (the host
+  // sizes the chunks so that this leaves rays to others).
+  constexpr uint32_t kWaves = WG / 64u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t die = blockIdx.x % kRtQueues, slot = blockIdx.x / kRtQueues;
+  // place of position p of queue v in the ray order; rays of queue v taken by
+  // the fixed shares
+  auto ray_at = [&](uint32_t v, uint32_t p) {
+    return ((((p >> P.tile_shift) * kRtQueues) + v) << P.tile_shift) + (p & ((1u << P.tile_shift) - 1u));
+  };
+  auto shared_out = [&](uint32_t v) { return (gridDim.x + kRtQueues - 1u - v) / kRtQueues * kWaves * P.share; };
+  uint32_t q_next, queue = die;
+  if (P.chunk == 0u) {
+    const uint32_t per = gridDim.x / kRtQueues, rem = gridDim.x % kRtQueues;
+    q_next = ((die * per + min(die, rem) + slot) * kWaves + wave) * P.share;
+  } else {
+    q_next = ray_at(die, (slot * kWaves + wave) * P.share);
+  }
+  q_next = min(P.n, q_next);
+  uint32_t q_end = min(P.n, q_next + P.share);
+  bool drained = P.chunk == 0u;
+  uint32_t range = q_next, n_ranges = 1;
+  // The next rays, read 64 at a time into the wave's lanes: lanes that need
+  // one take it from there, without waiting for memory.
+  uint32_t w_base = 0, w_used = 0, w_len = 0;
+  float4 w_o, w_d;
+  uint32_t w_batch = 0;
+  auto next_window = [&]() {
+    while (q_next == q_end && !drained) {
+      // the next queue not known to be used up, from the last one on
+      constexpr uint32_t kAll = (1u << kRtQueues) - 1u;
+      uint32_t m = kAll & ~__builtin_amdgcn_readfirstlane(__hip_atomic_load(&lds_empty, __ATOMIC_RELAXED,
+                                                                            __HIP_MEMORY_SCOPE_WORKGROUP));
+      m = (m >> queue | m << (kRtQueues - queue)) & kAll;
+      drained = m == 0u;
+      if (drained) break;
+      queue = (queue + (uint32_t)__builtin_ctz(m)) % kRtQueues;
+      uint32_t head = 0;
+      if (lane == 0) head = atomicAdd(P.counter + queue * kRtQueueStride, P.chunk);
+      const uint32_t base = ray_at(queue, shared_out(queue) + __builtin_amdgcn_readfirstlane(head));
+      if (base < P.n) {
+        q_next = base;
+        q_end = min(P.n, base + P.chunk);
+        if constexpr (FUSED) {
+          if (lane == n_ranges) range = base;
+          ++n_ranges;
+          drained = n_ranges == kRtRangesPerWave;
+        }
+      } else {
+        bool out = false;
+        if (lane < kRtQueues) {
+          const uint32_t h = __hip_atomic_load(P.counter + lane * kRtQueueStride, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+          out = ray_at(lane, shared_out(lane) + h) >= P.n;
+        }
+        const uint32_t used = (uint32_t)__ballot(out);
+        if (lane == 0) atomicOr(&lds_empty, used);
+      }
+    }
+    w_base = q_next;
+    w_len = min(q_end - q_next, 64u);
+    w_used = 0;
+    q_next += w_len;
+    if (lane < w_len) {
+      uint32_t i = w_base + lane;
+      const rt_ray* rays = P.rays;
+      if constexpr (MODE == 1) {
+        // the batch whose ray range holds i (offsets has batch_count+1 entries)
+        uint32_t lo = 0, hi = P.batch_count;
+        while (hi - lo > 1) {
+          uint32_t mid = (lo + hi) >> 1;
+          if (P.batch_offsets[mid] <= i) lo = mid; else hi = mid;
+        }
+        w_batch = lo;
+        i -= P.batch_offsets[lo];
+        rays = P.batches[lo].rays;
+      }
+      const float4* p = reinterpret_cast<const float4*>(rays + i);
+      w_o = p[0];
+      w_d = p[1];
+    }
   };
 
   while (true) {
+    // lanes by what they can do next
+    uint32_t n_node, n_tri, n_idle, n_frame;
+    uint64_t m_idle;
+    auto count = [&]() {
+      const uint64_t m_node = __ballot((int32_t)cur >= 0);
+      // RT_LEAF_BIT set, RT_INST_BIT clear
+      const uint64_t m_tri = __ballot(leaf != 0u) | __ballot((int32_t)cur < (int32_t)0xC0000000);
+      m_idle = __ballot(cur == RT_CHILD_EMPTY) & ~m_tri;
+      n_node = __popcll(m_node);
+      n_tri = __popcll(m_tri);
+      n_idle = __popcll(m_idle);
+      n_frame = INST ? 64u - n_node - n_tri - n_idle + (uint32_t)__popcll(m_node & m_tri) : 0u;
+    };
+    count();
     if constexpr (COUNT) w_outer += lane == 0 ? 1u : 0u;
-    // ---- refill finished lanes (one atomic per wave) --------------------
-    bool need = !live && !retired;
-    uint64_t m = __ballot(need);
-    uint64_t mlive = __ballot(live);
-    uint32_t n_need = __popcll(m);
-    if (n_need > 0 && (mlive == 0 || n_need >= P.refill_min)) {
-      if constexpr (COUNT) w_refill += lane == 0 ? 1u : 0u;
-      uint32_t leader = __ffsll((unsigned long long)m) - 1;
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(P.counter, n_need);
-      base = (uint32_t)__shfl((int)base, (int)leader);
-      if constexpr (FUSED) {
-        // remember the range [base, base + take) this wave now owns
-        if (base < P.n) {
-          uint32_t take = min(n_need, P.n - base);
-          if (n_ranges < kRtRangesPerWave) {
-            if (lane == 0) {
-              my_ranges[2 * n_ranges] = base;
-              my_ranges[2 * n_ranges + 1] = take;
-            }
-            ++n_ranges;
-          } else if (lane == 0) {
-            uint32_t k = atomicAdd(P.counter + 1, 1u);
-            if (k < P.ovf_cap) {
-              P.ovf[2 * k] = base;
-              P.ovf[2 * k + 1] = take;
-            }
-          }
-        }
-      }
-      if (need) {
-        uint32_t my = base + __popcll(m & lanemask_lt);
-        if (my < P.n) {
-          ray_id = my;
-          uint32_t local = my;
-          if constexpr (MODE == 1) {
-            // the batch whose ray range holds `my` (offsets has batch_count+1 entries)
-            uint32_t lo = 0, hi = P.batch_count;
-            while (hi - lo > 1) {
-              uint32_t mid = (lo + hi) >> 1;
-              if (P.batch_offsets[mid] <= my) lo = mid; else hi = mid;
-            }
-            batch = lo;
-            const BatchDesc& bd = P.batches[lo];
-            local = my - P.batch_offsets[lo];
-            g.nodes = bd.nodes;
-            g.tris = reinterpret_cast<const float4*>(bd.tris);
-            g.meshes = bd.meshes;
-            g.root = bd.root;
-            if constexpr (INST) {
-              g.insts = bd.insts;
-              g.insts64 = bd.insts64;
-            }
-            ray_in = bd.rays;
-            hit_out = bd.hits;
-          }
-          rt_ray wray = load_ray(ray_in, local);
-          ray_id = local;
-          world_state(wray, r);
-          if constexpr (INST) {
-            lds_world[0 * WG + tid] = wray.ox;
-            lds_world[1 * WG + tid] = wray.oy;
-            lds_world[2 * WG + tid] = wray.oz;
-            lds_world[3 * WG + tid] = wray.dx;
-            lds_world[4 * WG + tid] = wray.dy;
-            lds_world[5 * WG + tid] = wray.dz;
-          }
-          best_t = r.tmax;
-          best_rec = RT_INVALID_ID;
-          best_inst = RT_INVALID_ID;
-          cur_inst = 0;
-          in_inst = false;
-          st.sp = 0;
-#pragma unroll
-          for (int k = 0; k < K; ++k) pq[k] = RT_CHILD_EMPTY;
-          cur = ray_void(wray) ? RT_CHILD_EMPTY : g.root;
-          if constexpr (MODE >= 2) {
-            rmask = P.ray_masks ? P.ray_masks[local] : 0xFFFFFFFFu;
-            skip_p = P.skip_prim ? P.skip_prim[local] : RT_INVALID_ID;
-            skip_i = P.skip_inst ? P.skip_inst[local] : RT_INVALID_ID;
-            found = 0;
-            // a single-level accel is one geometry of mask 0xFFFFFFFF
-            if (!INST && rmask == 0u) cur = RT_CHILD_EMPTY;
-          }
-          live = true;
-        } else {
-          retired = true;
-        }
-      }
-    }
-    if (__ballot(live) == 0) {
-      if (__ballot(!retired) == 0) break;
-      continue;
-    }
-    if (live) {
-      float tcull = fmaf(fabsf(best_t), kTieWiden, best_t);
-      uint32_t linst = cur_inst;   // instance of the leaf under test
-      // sets r's origin and direction to those of the world ray in instance
-      // j's object space (the reciprocals stay those of the traversal frame)
-      auto frame_od = [&](bool inside, uint32_t j) {
-        const float wox = lds_world[0 * WG + tid], woy = lds_world[1 * WG + tid], woz = lds_world[2 * WG + tid];
-        const float wdx = lds_world[3 * WG + tid], wdy = lds_world[4 * WG + tid], wdz = lds_world[5 * WG + tid];
-        if (inside) {
-          to_object_od(g.insts[j], wox, woy, woz, wdx, wdy, wdz, r);
-        } else {
-          r.ox = wox; r.oy = woy; r.oz = woz;
-          r.dx = wdx; r.dy = wdy; r.dz = wdz;
-        }
-      };
-      // Tests the triangles of one leaf; true when an any-hit query may stop.
-      // Tests triangle record `rec`; true when an any-hit query may stop.
-      auto test_tri = [&](uint32_t rec) -> bool {
-        const float4* tp = g.tris + 3 * (size_t)rec;
-        if constexpr (COUNT) n_tris++;
-        float4 A = tp[0], B = tp[1], C = tp[2];
-        float t;
-        if (tri_test(A, B, C, r, t) && t >= r.tmin && t <= best_t) {
-          uint32_t prim = __float_as_uint(A.w);
-          if constexpr (MODE >= 2) {
-            if (prim == skip_p && (!INST || linst == skip_i)) return false;
-          }
-          if constexpr (MODE == 3) {
-            list_insert(reinterpret_cast<float4*>(hit_out) + (size_t)ray_id * P.cap, found, P.cap, t,
-                        INST ? linst : 0u, prim, rec);
-            ++found;
-            return false;
-          }
-          if constexpr (ANY) {
-            best_rec = rec;
-            return true;
-          } else {
-            // lexicographic (t, inst, prim); t <= best_t here
-            uint32_t inst = INST ? linst : 0u;
-            bool better = (t < best_t) || (inst < best_inst);
-            if (!better && inst == best_inst)
-              better = prim < __float_as_uint(g.tris[3 * (size_t)best_rec].w);
-            if (better) {
-              best_t = t;
-              best_inst = inst;
-              best_rec = rec;
-            }
-          }
-        }
-        return false;
-      };
-      // Visits internal node `cur`: continues with the nearest child hit and
-      // pushes the others, farthest first.
-      auto step_node = [&]() {
-        uint32_t refs[W];
-        int nh;
-        if constexpr (COUNT) n_nodes++;
-        visit_node<W, ANY && !INST>(g.nodes, cur, r, tcull, refs, nh);
-        if (nh == 0) {
-          cur = st.pop();
-        } else {
-          cur = refs[0];
-#pragma unroll
-          for (int i = W - 1; i >= 1; --i)
-            if (i < nh) {
-              if constexpr (COUNT) n_spill += (st.sp >= S) ? 1 : 0;
-              st.push(refs[i]);
-            }
-        }
-      };
-      // ---- internal nodes, leaves postponed ---------------------------------
-      // A lane that reaches a leaf sets it aside and keeps traversing until
-      // it holds K leaves and meets another, or every lane of the wave holds
-      // a leaf, so that the wave enters the triangle loop together (leaf
-      // postponing, Aila & Laine 2009, with more than one leaf a lane: the
-      // node loop then runs with more lanes busy, the triangle loop with more
-      // triangles a lane).  A postponed leaf remembers its instance, and the
-      // triangle loop takes the world ray into that instance's object space
-      // to test it (the float32 map of the instance entry, applied to the
-      // same world ray, so the object ray is the same), so a lane holding one
-      // keeps traversing across instance boundaries.
-      while (cur != RT_CHILD_EMPTY) {
-        if constexpr (COUNT) w_node += first_active() ? 1u : 0u;
-        if constexpr (INST) {
-          if (cur == RT_STACK_MARKER || is_inst(cur)) {
-            if (cur == RT_STACK_MARKER) {
-              r.ox = lds_world[0 * WG + tid];
-              r.oy = lds_world[1 * WG + tid];
-              r.oz = lds_world[2 * WG + tid];
-              r.dx = lds_world[3 * WG + tid];
-              r.dy = lds_world[4 * WG + tid];
-              r.dz = lds_world[5 * WG + tid];
-              ray_setup(r);
-              in_inst = false;
-              r.tmax = best_t;
-              cur = st.pop();
+    // a wave refills once this many lanes are idle, while there are rays
+    const uint32_t idle_max = (w_used != w_len || q_next != q_end || !drained) ? min(P.refill_min, 64u) : 64u;
+    if (n_idle >= idle_max) {
+      // ---- store finished rays, take new ones ---------------------------
+      if (w_used == w_len) next_window();
+      const uint32_t take = min(n_idle, w_len - w_used);
+      const bool end = take == 0u && n_idle == 64u;
+      if (take != 0u || end) {
+        if constexpr (COUNT) w_refill += (lane == 0 && take != 0u) ? 1u : 0u;
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_idle >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m_idle, 0u));
+        const int src = (int)((w_used + rank) << 2);
+        auto from = [&](float x) { return __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(x))); };
+        rt_ray wray;
+        wray.ox = from(w_o.x); wray.oy = from(w_o.y); wray.oz = from(w_o.z); wray.tmin = from(w_o.w);
+        wray.dx = from(w_d.x); wray.dy = from(w_d.y); wray.dz = from(w_d.z); wray.tmax = from(w_d.w);
+        const uint32_t bat = MODE == 1 ? (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)w_batch) : 0u;
+        if (cur == RT_CHILD_EMPTY && leaf == 0u) {
+          // the finished ray's result (the float64 (t, u, v) and the prim id
+          // of a closest hit are written by the finalize: for one-accel
+          // closest queries (MODE 0) by this wave once all rays of its
+          // ranges are done, below; for batched, masked and counting
+          // launches by finalize_kernel, one thread per ray.  Here: float32
+          // t, the triangle record in the prim slot and the instance in the
+          // u slot)
+          if (ray_id != RT_INVALID_ID) {
+            if constexpr (MODE == 3) {
+              P.counts[ray_id] = found;
+            } else if constexpr (ANY) {
+              P.occluded[ray_id] = (best_rec != RT_INVALID_ID) ? 1 : 0;
             } else {
-              uint32_t j = cur & RT_INST_INDEX_MASK;
-              const rt_inst_rec& I = g.insts[j];
-              bool skip = I.root == RT_CHILD_EMPTY;
-              if constexpr (MODE >= 2) skip = skip || (I.mask & rmask) == 0u;
-              if (skip) {
-                cur = st.pop();
-              } else {
-                to_object(I, r);
-                r.tmax = best_t;
-                cur_inst = j;
-                in_inst = true;
-                st.push(RT_STACK_MARKER);
-                cur = I.root;
-              }
-            }
-            // a node or a leaf after the frame change is taken in the same
-            // iteration; another frame change or the end waits for the next
-            if (cur == RT_CHILD_EMPTY || cur == RT_STACK_MARKER || is_inst(cur)) continue;
-          }
-        }
-        auto postpone = [&]() {
-          bool placed = false;
-#pragma unroll
-          for (int k = 0; k < K; ++k)
-            if (!placed && pq[k] == RT_CHILD_EMPTY) {
-              pq[k] = cur;
-              if constexpr (INST) pin[k] = cur_inst;
-              placed = true;
-            }
-          cur = st.pop();
-        };
-        if constexpr (INST || (!ANY && MODE != 1)) {
-          // an internal node under a postponed leaf is visited in the same
-          // iteration, so that a lane's iterations are node visits (batched
-          // single-level plans: -2% with it)
-          bool visit = true;
-          if (is_tri_leaf(cur)) {
-            if (pq[K - 1] != RT_CHILD_EMPTY) break;
-            postpone();
-            visit = is_internal(cur);
-          }
-          if (visit) step_node();
-        } else {
-          // (single-level any-hit: the same fall-through measured -0.6% on
-          // incoherent and +1.2% on shadow rays; the simpler loop stays)
-          if (is_tri_leaf(cur)) {
-            if (pq[K - 1] != RT_CHILD_EMPTY) break;
-            postpone();
-          } else {
-            step_node();
-          }
-        }
-        if (__ballot(pq[0] == RT_CHILD_EMPTY) == 0) break;
-      }
-      // ---- triangle leaves: the postponed ones, then those on the stack top -
-      // One triangle per iteration: a lane whose leaf is done moves on to
-      // its next leaf while others finish longer leaves (leaves hold 1-15
-      // triangles), instead of waiting for the longest leaf of the wave.
-      // The nearest-hit cull distance is updated after each leaf, as before.
-      // r's origin and direction are in frame rf (RT_INVALID_ID: world)
-      const uint32_t home = in_inst ? cur_inst : RT_INVALID_ID;
-      uint32_t rf = home;
-      auto take_postponed = [&](uint32_t& first, uint32_t& count) {
-        first = pq[0] & RT_LEAF_FIRST_MASK;
-        count = pq[0] != RT_CHILD_EMPTY ? (pq[0] >> RT_LEAF_COUNT_SHIFT) & RT_LEAF_COUNT_MASK : 0u;
-        if constexpr (INST) {
-          if (pq[0] != RT_CHILD_EMPTY) {
-            linst = pin[0];
-            if (rf != pin[0]) {
-              frame_od(true, pin[0]);
-              rf = pin[0];
+              const bool hit = best_rec != RT_INVALID_ID;
+              float4* hp = reinterpret_cast<float4*>(hit_out + ray_id);
+              *hp = make_float4(hit ? best_t : __int_as_float(0x7f800000), __uint_as_float(best_rec),
+                                __uint_as_float(hit && INST ? best_inst : 0u), 0.0f);
             }
           }
-#pragma unroll
-          for (int k = 0; k + 1 < K; ++k) pin[k] = pin[k + 1];
-        }
-#pragma unroll
-        for (int k = 0; k + 1 < K; ++k) pq[k] = pq[k + 1];
-        pq[K - 1] = RT_CHILD_EMPTY;
-      };
-      uint32_t tnext, tleft;
-      take_postponed(tnext, tleft);
-      while (tleft > 0) {
-        if constexpr (COUNT) w_leaf += first_active() ? 1u : 0u;
-        bool stop = test_tri(tnext);
-        ++tnext;
-        --tleft;
-        if (ANY && stop) {
-          cur = RT_CHILD_EMPTY;
-#pragma unroll
-          for (int k = 0; k < K; ++k) pq[k] = RT_CHILD_EMPTY;
-          st.sp = 0;
-          break;
-        }
-        if (tleft == 0) {
-          tcull = fmaf(fabsf(best_t), kTieWiden, best_t);
-          if (pq[0] != RT_CHILD_EMPTY) {
-            take_postponed(tnext, tleft);
-          } else if (cur != RT_CHILD_EMPTY && is_tri_leaf(cur)) {
+          ray_id = RT_INVALID_ID;
+          if (rank < take) {
+            ray_id = w_base + w_used + rank;
+            if constexpr (MODE == 1) {
+              const BatchDesc& bd = P.batches[bat];
+              ray_id -= P.batch_offsets[bat];
+              g.nodes = bd.nodes;
+              g.tris = reinterpret_cast<const float4*>(bd.tris);
+              g.root = bd.root;
+              if constexpr (INST) g.insts = bd.insts;
+              hit_out = bd.hits;
+            }
+            world_state(wray, r);
             if constexpr (INST) {
-              // the leaves on the stack top are in the traversal frame
-              if (rf != home) {
-                frame_od(in_inst, cur_inst);
-                rf = home;
-              }
-              linst = cur_inst;
+              lds_world[0 * WG + tid] = wray.ox;
+              lds_world[1 * WG + tid] = wray.oy;
+              lds_world[2 * WG + tid] = wray.oz;
+              lds_world[3 * WG + tid] = wray.dx;
+              lds_world[4 * WG + tid] = wray.dy;
+              lds_world[5 * WG + tid] = wray.dz;
             }
-            tnext = cur & RT_LEAF_FIRST_MASK;
-            tleft = (cur >> RT_LEAF_COUNT_SHIFT) & RT_LEAF_COUNT_MASK;
-            cur = st.pop();
+            best_t = wray.tmax;
+            tcull = fmaf(fabsf(best_t), kTieWiden, best_t);
+            best_rec = RT_INVALID_ID;
+            best_inst = RT_INVALID_ID;
+            cur = ray_void(wray) ? RT_CHILD_EMPTY : g.root;
+            if constexpr (MODE >= 2) {
+              rmask = P.ray_masks ? P.ray_masks[ray_id] : 0xFFFFFFFFu;
+              skip_p = P.skip_prim ? P.skip_prim[ray_id] : RT_INVALID_ID;
+              skip_i = P.skip_inst ? P.skip_inst[ray_id] : RT_INVALID_ID;
+              found = 0;
+              // a single-level accel is one geometry of mask 0xFFFFFFFF
+              if (!INST && rmask == 0u) cur = RT_CHILD_EMPTY;
+            }
+          }
+        }
+        w_used += take;
+        if (end) break;
+        count();
+      }
+    }
+    // entries popped must lie no farther than this (the margin over the
+    // nearest hit is that of float32 rounding in t, well above the box test's)
+    float far = fmaf(fabsf(best_t), kPopWiden, best_t);
+    if (n_node >= 2u * max(n_tri, n_frame)) {
+      // ---- node visits ----------------------------------------------------
+      do {
+        if constexpr (COUNT) w_node += lane == 0 ? 1u : 0u;
+        if ((int32_t)cur >= 0) {
+          if constexpr (COUNT) n_nodes++;
+          double e[W];
+          visit_node<W, OFF32>(g.nodes, cur, r, tcull, e);
+          auto dist = [&](int i) { return __int_as_float(__double2hiint(e[i])); };
+          auto ref = [&](int i) { return (uint32_t)__double2loint(e[i]); };
+          auto entered = [&](int i) { return dist(i) < __int_as_float(0x7f800000); };
+          auto entry = [&](int i) -> E {
+            if constexpr (CULL) return (uint64_t)__double_as_longlong(e[i]); else return ref(i);
+          };
+          // the children behind the nearest, farthest first
+          if (__ballot(!st.fits(W - 1)) == 0ull) {
+#pragma unroll
+            for (int i = W - 1; i >= 1; --i)
+              if (entered(i)) st.push_lds(entry(i));
+          } else {
+#pragma unroll
+            for (int i = W - 1; i >= 1; --i)
+              if (entered(i)) st.push(entry(i));
+          }
+          // continue with the nearest; a leaf is taken in hand when the hand
+          // is empty
+          cur = ref(0);
+          bool more = !entered(0);
+          if ((int32_t)cur < (int32_t)0xC0000000 && leaf == 0u && !more) {
+            leaf = cur & ~RT_LEAF_BIT;
+            more = true;
+          }
+          if (more) cur = st.pop(far, tid);
+        }
+        count();
+      } while (n_node >= 2u * max(n_tri, n_frame) && n_idle < idle_max);
+    } else if (!INST || n_tri >= n_frame) {
+      // ---- triangle tests --------------------------------------------------
+      do {
+        if constexpr (COUNT) w_leaf += lane == 0 ? 1u : 0u;
+        if (leaf != 0u || (int32_t)cur < (int32_t)0xC0000000) {
+          if constexpr (COUNT) n_tris++;
+          if (leaf == 0u) {
+            leaf = cur & ~RT_LEAF_BIT;
+            cur = st.pop(far, tid);
+          }
+          const uint32_t rec = leaf & RT_LEAF_FIRST_MASK;
+          const float4* tp = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(g.tris) + (size_t)(rec * 48u));
+          const float4 A = tp[0], B = tp[1], C = tp[2];
+          leaf += 1u - (1u << RT_LEAF_COUNT_SHIFT);
+          if (leaf < (1u << RT_LEAF_COUNT_SHIFT)) leaf = 0;
+          float t;
+          if (tri_test(A, B, C, r, t) && t >= r.tmin && t <= best_t) {
+            const uint32_t prim = __float_as_uint(A.w);
+            bool use = true;
+            if constexpr (MODE >= 2) use = !(prim == skip_p && (!INST || cur_inst == skip_i));
+            if constexpr (MODE == 3) {
+              if (use) {
+                list_insert(reinterpret_cast<float4*>(hit_out) + (size_t)ray_id * P.cap, found, P.cap, t,
+                            INST ? cur_inst : 0u, prim, rec);
+                ++found;
+              }
+            } else if constexpr (ANY) {
+              if (use) {
+                best_rec = rec;
+                cur = RT_CHILD_EMPTY;
+                leaf = 0;
+                st.clear(tid);
+              }
+            } else if (use) {
+              // lexicographic (t, inst, prim); t <= best_t here
+              const uint32_t inst = INST ? cur_inst : 0u;
+              bool better = (t < best_t) || (inst < best_inst);
+              if (!better && inst == best_inst) better = prim < __float_as_uint(g.tris[3 * (size_t)best_rec].w);
+              if (better) {
+                best_t = t;
+                tcull = fmaf(fabsf(t), kTieWiden, t);
+                far = fmaf(fabsf(t), kPopWiden, t);
+                best_inst = inst;
+                best_rec = rec;
+              }
+            }
+          }
+        }
+        count();
+      } while (n_node < 2u * n_tri && n_tri >= n_frame && n_idle < idle_max);
+    } else if constexpr (INST) {
+      // ---- instance entries and exits -------------------------------------
+      // (a leaf in hand is tested in its own frame first: such lanes count
+      // among the triangle tests)
+      if ((int32_t)cur < 0 && (int32_t)cur >= (int32_t)0xC0000000 && leaf == 0u && cur != RT_CHILD_EMPTY) {
+        if (cur == RT_STACK_MARKER) {
+          r.ox = lds_world[0 * WG + tid];
+          r.oy = lds_world[1 * WG + tid];
+          r.oz = lds_world[2 * WG + tid];
+          r.dx = lds_world[3 * WG + tid];
+          r.dy = lds_world[4 * WG + tid];
+          r.dz = lds_world[5 * WG + tid];
+          ray_setup(r);
+          cur = st.pop(far, tid);
+        } else {
+          const uint32_t j = cur & RT_INST_INDEX_MASK;
+          const rt_inst_rec& I = g.insts[j];
+          bool skip = I.root == RT_CHILD_EMPTY;
+          if constexpr (MODE >= 2) skip = skip || (I.mask & rmask) == 0u;
+          if (skip) {
+            cur = st.pop(far, tid);
+          } else {
+            to_object(I, r);
+            cur_inst = j;
+            E m = RT_STACK_MARKER;
+            if constexpr (CULL) m |= (uint64_t)0xff800000u << 32;
+            st.push(m);
+            cur = I.root;
           }
         }
       }
-      if constexpr (INST) {
-        if (rf != home) frame_od(in_inst, cur_inst);   // back to the traversal frame
-      }
-      // ---- finished: write the result --------------------------------------
-      // (the float64 (t, u, v) and the prim id of a closest hit are written
-      // by the finalize: for one-accel closest queries (MODE 0) by this wave
-      // once all rays of its ranges are done, below, and by
-      // finalize_ovf_kernel for ranges past its list; for batched, masked
-      // and counting launches by finalize_kernel, one thread per ray.  Here:
-      // float32 t, the triangle record in the prim slot and the instance in
-      // the u slot)
-      if (cur == RT_CHILD_EMPTY && pq[0] == RT_CHILD_EMPTY) {
-        if constexpr (MODE == 3) {
-          P.counts[ray_id] = found;
-        } else if constexpr (ANY) {
-          occ_out[ray_id] = (best_rec != RT_INVALID_ID) ? 1 : 0;
-        } else {
-          bool hit = best_rec != RT_INVALID_ID;
-          float4* hp = reinterpret_cast<float4*>(hit_out + ray_id);
-          *hp = make_float4(hit ? best_t : __int_as_float(0x7f800000), __uint_as_float(best_rec),
-                            __uint_as_float(hit ? (INST ? best_inst : 0u) : 0u), 0.0f);
-        }
-        live = false;
+    }
+  }
+  if (P.chunk != 0u && lane == 0) {
+    // the last wave of the launch to leave the queues zeroes them for the
+    // next launch
+    if (atomicAdd(&lds_done, 1u) == kWaves - 1u) {
+      if (atomicAdd(P.counter + kRtQueues * kRtQueueStride, 1u) == gridDim.x - 1u) {
+        for (uint32_t v = 0; v <= kRtQueues; ++v)
+          __hip_atomic_store(P.counter + v * kRtQueueStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
@@ -837,22 +855,20 @@ __global__ __launch_bounds__(WG, (trace_min_waves<W, INST, COUNT, MODE>())) void
     if (st.over) __hip_atomic_store(P.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   if constexpr (FUSED) {
-    // every ray this wave took is finished: float64 finalize of its listed
-    // ranges with full waves, while other waves still trace (the wave's own
-    // hit stores precede these loads)
+    // every ray this wave took is finished: float64 finalize of its ranges
+    // with full waves, while other waves still trace (the wave's own hit
+    // stores precede these loads)
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     for (uint32_t k = 0; k < n_ranges; ++k) {
-      uint32_t b = my_ranges[2 * k], c = my_ranges[2 * k + 1];
-      for (uint32_t o = 0; o < c; o += 64) {
-        if (o + lane < c)
-          finalize_index<INST, MODE>(P, b + o + lane);
-      }
+      const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)range, (int)k);
+      const uint32_t end = min(P.n, b + P.share);   // (chunks are as long as the share)
+      for (uint32_t i = b + lane; i < end; i += 64) finalize_index<INST, MODE>(P, i);
     }
   }
   if constexpr (COUNT) {
     atomicAdd(reinterpret_cast<unsigned long long*>(P.counters) + 0, (unsigned long long)n_nodes);
     atomicAdd(reinterpret_cast<unsigned long long*>(P.counters) + 1, (unsigned long long)n_tris);
-    atomicAdd(reinterpret_cast<unsigned long long*>(P.counters) + 2, (unsigned long long)n_spill);
+    atomicAdd(reinterpret_cast<unsigned long long*>(P.counters) + 2, (unsigned long long)st.spills);
     atomicMax(reinterpret_cast<unsigned long long*>(P.counters) + 3, (unsigned long long)st.peak);
     if (P.phase_counters) {
       uint64_t w[4] = {w_outer, w_refill, w_node, w_leaf};
@@ -863,7 +879,6 @@ __global__ __launch_bounds__(WG, (trace_min_waves<W, INST, COUNT, MODE>())) void
       }
     }
   }
-  (void)batch;
 }
 
 // ---------------------------------------------------------------------------
@@ -1285,18 +1300,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(TraceParams P) {
   finalize_index<INST, MODE>(P, i);
 }
 
-// float64 finalize of the ranges that fused closest-hit traversal waves could
-// not keep in their lists: one wave per range (a range holds at most 64 rays)
-template <bool INST>
-__global__ __launch_bounds__(64) void finalize_ovf_kernel(TraceParams P) {
-  uint32_t count = min(P.counter[1], P.ovf_cap);
-  for (uint32_t k = blockIdx.x; k < count; k += gridDim.x) {
-    uint32_t b = P.ovf[2 * k], c = P.ovf[2 * k + 1];
-    for (uint32_t o = threadIdx.x; o < c; o += 64)
-      finalize_index<INST, 0>(P, b + o);
-  }
-}
-
 // float64 finalize of all-hit lists: one thread per list entry; entries past
 // a ray's stored hits become misses (t = +inf, prim and instance invalid).
 template <bool INST>
@@ -1526,11 +1529,6 @@ __global__ __launch_bounds__(256) void ao_resolve_kernel(const uint8_t* occ, uin
   ao[i] = (float)c / (float)samples;
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, uint32_t n, uint32_t value) {
-  uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = value;
-}
-
 }  // namespace rtk
 
 // ---------------------------------------------------------------------------
@@ -1538,21 +1536,14 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t n, uint32_t value) {
 // ---------------------------------------------------------------------------
 namespace {
 
-template <int W, int S, int WG, bool ANY, bool INST, int MODE>
+template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool OFF32>
 const void* kernel_ptr() {
-  return reinterpret_cast<const void*>(&rtk::trace_kernel<W, S, WG, ANY, INST, MODE>);
-}
-
-template <int W>
-const void* pick_query(bool any, bool inst, int mode) {
-  if (mode == 3) return inst ? kernel_ptr<W, 16, 256, false, true, 3>() : kernel_ptr<W, 16, 256, false, false, 3>();
-  if (any) return inst ? kernel_ptr<W, 16, 256, true, true, 2>() : kernel_ptr<W, 16, 256, true, false, 2>();
-  return inst ? kernel_ptr<W, 16, 256, false, true, 2>() : kernel_ptr<W, 16, 256, false, false, 2>();
+  return reinterpret_cast<const void*>(&rtk::trace_kernel<W, S, WG, ANY, INST, MODE, OFF32>);
 }
 
 template <int W, bool ANY, bool INST>
 const void* kernel_ptr_c() {
-  return reinterpret_cast<const void*>(&rtk::trace_kernel<W, 16, 256, ANY, INST, 0, true>);
+  return reinterpret_cast<const void*>(&rtk::trace_kernel<W, 16, 256, ANY, INST, 0, false, true>);
 }
 template <int W>
 const void* count_kernel_w(bool any, bool inst) {
@@ -1560,11 +1551,27 @@ const void* count_kernel_w(bool any, bool inst) {
   return any ? kernel_ptr_c<W, true, false>() : kernel_ptr_c<W, false, false>();
 }
 
+// modes 0, 2 and 3 of one (stack, workgroup)
+template <int W, int S, int WG, int MODE, bool OFF32>
+const void* pick_any(bool any, bool inst) {
+  if constexpr (MODE != 3) {
+    if (any) return inst ? kernel_ptr<W, S, WG, true, true, MODE, OFF32>() : kernel_ptr<W, S, WG, true, false, MODE, OFF32>();
+  }
+  return inst ? kernel_ptr<W, S, WG, false, true, MODE, OFF32>() : kernel_ptr<W, S, WG, false, false, MODE, OFF32>();
+}
+
+template <int W, bool OFF32>
+const void* pick_default(bool any, bool inst, int mode) {
+  return mode == 3   ? pick_any<W, 16, 256, 3, OFF32>(any, inst)
+         : mode == 2 ? pick_any<W, 16, 256, 2, OFF32>(any, inst)
+                     : pick_any<W, 16, 256, 0, OFF32>(any, inst);
+}
+
 template <int W, int S, int WG>
 const void* pick_mode(bool any, bool inst, int mode) {
-  if (mode == 1) return inst ? kernel_ptr<W, S, WG, false, true, 1>() : kernel_ptr<W, S, WG, false, false, 1>();
-  if (any) return inst ? kernel_ptr<W, S, WG, true, true, 0>() : kernel_ptr<W, S, WG, true, false, 0>();
-  return inst ? kernel_ptr<W, S, WG, false, true, 0>() : kernel_ptr<W, S, WG, false, false, 0>();
+  if (mode == 1)
+    return inst ? kernel_ptr<W, S, WG, false, true, 1, false>() : kernel_ptr<W, S, WG, false, false, 1, false>();
+  return pick_any<W, S, WG, 0, true>(any, inst);
 }
 
 template <int W, int S>
@@ -1578,7 +1585,12 @@ const void* pick_wg(int wg, bool any, bool inst, int mode) {
 }
 
 template <int W>
-const void* pick_s(int s, int wg, bool any, bool inst, int mode) {
+const void* pick_s(int s, int wg, bool any, bool inst, int mode, bool wide) {
+  if (mode == 3 && any) return nullptr;
+  if (mode != 1 && (wide || mode >= 2)) {
+    if (s != 16 || wg != 256) return nullptr;
+    return wide ? pick_default<W, false>(any, inst, mode) : pick_default<W, true>(any, inst, mode);
+  }
   switch (s) {
     case 8: return pick_wg<W, 8>(wg, any, inst, mode);
     case 16: return pick_wg<W, 16>(wg, any, inst, mode);
@@ -1600,20 +1612,11 @@ const void* rtk_count_kernel(int width, bool any, bool inst) {
   }
 }
 
-const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode) {
-  if (mode >= 2) {
-    if (stack != 16 || wg != 256 || (mode == 3 && any)) return nullptr;
-    switch (width) {
-      case 2: return pick_query<2>(any, inst, mode);
-      case 4: return pick_query<4>(any, inst, mode);
-      case 8: return pick_query<8>(any, inst, mode);
-      default: return nullptr;
-    }
-  }
+const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode, bool wide) {
   switch (width) {
-    case 2: return pick_s<2>(stack, wg, any, inst, mode);
-    case 4: return pick_s<4>(stack, wg, any, inst, mode);
-    case 8: return pick_s<8>(stack, wg, any, inst, mode);
+    case 2: return pick_s<2>(stack, wg, any, inst, mode, wide);
+    case 4: return pick_s<4>(stack, wg, any, inst, mode, wide);
+    case 8: return pick_s<8>(stack, wg, any, inst, mode, wide);
     default: return nullptr;
   }
 }
@@ -1668,16 +1671,6 @@ bool rtk_trace_fuses_finalize(bool any, bool inst, int mode) {
   return !any && mode == 0;
 }
 
-hipError_t rtk_launch_finalize_ovf(bool inst, const TraceParams& p, hipStream_t stream) {
-  if (p.n == 0 || p.ovf_cap == 0) return hipSuccess;
-  TraceParams q = p;
-  void* args[] = {&q};
-  const void* k = inst ? reinterpret_cast<const void*>(&rtk::finalize_ovf_kernel<true>)
-                       : reinterpret_cast<const void*>(&rtk::finalize_ovf_kernel<false>);
-  // one wave per listed range at most (the list holds no more than ovf_cap)
-  return hipLaunchKernel(k, dim3(std::min<uint32_t>(2048u, p.ovf_cap)), dim3(64), args, 0, stream);
-}
-
 hipError_t rtk_launch_finalize_all(bool inst, const TraceParams& p, hipStream_t stream) {
   uint64_t total = (uint64_t)p.n * p.cap;
   if (total == 0) return hipSuccess;
@@ -1721,12 +1714,5 @@ hipError_t rtk_launch_ao_resolve(const uint8_t* occluded, uint32_t n, uint32_t s
   if (n == 0) return hipSuccess;
   void* args[] = {&occluded, &n, &samples, &ao};
   return hipLaunchKernel(reinterpret_cast<const void*>(&rtk::ao_resolve_kernel),
-                         dim3((n + 255) / 256), dim3(256), args, 0, stream);
-}
-
-hipError_t rtk_launch_fill(uint32_t* ptr, uint32_t n, uint32_t value, hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  void* args[] = {&ptr, &n, &value};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&rtk::fill_u32_kernel),
                          dim3((n + 255) / 256), dim3(256), args, 0, stream);
 }
