@@ -179,8 +179,15 @@ struct Collapse {
   double internal_area = 0.0;
 };
 
-// Writes wide node `wi` for binary node `bi` and recurses.
-void collapse(Collapse& C, uint32_t bi, uint32_t wi, uint32_t depth, uint32_t stack_above) {
+// A wide node still to be written.
+struct Pending {
+  uint32_t bi, wi, depth, stack_above;
+};
+
+// Writes wide node `p.wi` for binary node `p.bi`; its internal children are
+// numbered and appended to `next`.
+void expand(Collapse& C, const Pending& p, std::vector<Pending>& next) {
+  const uint32_t bi = p.bi, wi = p.wi, depth = p.depth, stack_above = p.stack_above;
   const std::vector<BNode>& N = C.B->nodes;
   const int W = C.W;
   std::vector<uint32_t> kids;
@@ -240,7 +247,29 @@ void collapse(Collapse& C, uint32_t bi, uint32_t wi, uint32_t depth, uint32_t st
     std::memcpy(&nd[7 * W + i], &zero, 4);
   }
   for (size_t i = 0; i < kids.size(); ++i)
-    if (child_node[i] != RT_CHILD_EMPTY) collapse(C, kids[i], child_node[i], depth + 1, stack_here);
+    if (child_node[i] != RT_CHILD_EMPTY) next.push_back(Pending{kids[i], child_node[i], depth + 1, stack_here});
+}
+
+void collapse(Collapse& C, const Pending& p) {
+  std::vector<Pending> next;
+  expand(C, p, next);
+  for (const Pending& q : next) collapse(C, q);
+}
+
+// The upper levels are numbered breadth first (the traversal keeps the first
+// nodes of the array close at hand), everything below them depth first.
+constexpr uint32_t kBreadthFirstNodes = 256;
+void collapse_tree(Collapse& C) {
+  std::vector<Pending> level{Pending{0, 0, 1, 0}};
+  while (!level.empty()) {
+    std::vector<Pending> next;
+    const bool breadth = C.out->node_count < kBreadthFirstNodes;
+    for (const Pending& p : level) {
+      if (breadth) expand(C, p, next);
+      else collapse(C, p);
+    }
+    level.swap(next);
+  }
 }
 
 bool lex_less(const float* a, const float* b) {
@@ -269,7 +298,7 @@ void finish_tree(Binary& B, int width, WideTree& out, const std::function<uint32
   C.W = width;
   C.out = &out;
   C.leaf_ref = leaf;
-  collapse(C, 0, 0, 1, 0);
+  collapse_tree(C);
   out.nodes.resize((size_t)out.node_count * 8 * width);
   out.root = 0;
   out.bounds = B.nodes[0].b;

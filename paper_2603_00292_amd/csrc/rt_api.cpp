@@ -213,13 +213,12 @@ void destroy_accel(rt_accel_s* a) {
 // crowd it: on 4M incoherent rays 4 / 5 / 6 / 7 workgroups of four waves took
 // 1,449 / 1,424 / 1,473 / 1,557 us, ambient occlusion 1,780 / 1,647 / 1,637 /
 // 1,758 us, 1,024 instances 3,069 / 2,760 / 2,858 / - us.
-constexpr uint32_t kWavesPerCu = 20;
 uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, wg, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 1;
-  return std::min((uint32_t)per_cu, kWavesPerCu * 64u / (uint32_t)wg) * (uint32_t)std::max(cu_count, 1);
+  return std::min((uint32_t)per_cu, (uint32_t)kRtWavesPerCu * 64u / (uint32_t)wg) * (uint32_t)std::max(cu_count, 1);
 }
 
 // Makes sure scratch holds zeroed counters and a spill stack of `words` words.
@@ -1290,6 +1289,8 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   p.chunk = shape.chunk;
   p.tile_shift = shape.tile_shift;
   p.gstack = gstack;
+  // (a launch of few rays does not earn the copy: 64 rays 27.1 against 26.5 us)
+  p.top_nodes = n < 32768u ? 0u : a->info.node_count;
   p.root = a->root;
   p.n = n;
   p.max_stack = stack_cap(ctx, a->max_stack, v.stack_entries);

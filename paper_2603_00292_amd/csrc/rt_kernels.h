@@ -46,6 +46,7 @@ struct TraceParams {
   const BatchDesc* batches;
   const uint32_t* batch_offsets;  // batch_count + 1 prefix sums of counts
   uint32_t batch_count;
+  uint32_t top_nodes;    // nodes [0, top_nodes) may be copied to LDS (upper levels first)
   uint32_t root;
   uint32_t n;            // rays in the launch (batched: total)
   uint32_t max_stack;    // stack entries a lane may need
@@ -75,11 +76,21 @@ constexpr uint32_t kRtRangesPerWave = 64;
 constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
 constexpr uint32_t kRtCounterWords = (kRtQueues + 1) * kRtQueueStride;
 
+// waves that run at once on a CU at most (see resident_blocks)
+constexpr int kRtWavesPerCu = 20;
+
 // LDS stack entries of a lane in the variant with `stack` entries: 4-byte
 // references for any-hit and all-hit queries; closest hits keep an 8-byte
 // (distance, reference) entry, and 5/8 as many, which holds eight workgroups
 // of 256 threads in a CU's 160 KB.
 constexpr int rtk_lds_entries(int stack, bool cull) { return cull ? stack * 5 / 8 : stack; }
+// Nodes of W-wide trees that fit the rest of a workgroup's LDS after `used`
+// bytes, when kRtWavesPerCu waves are to share a CU's 160 KB (which it gives
+// out in pieces of 1,280 bytes)
+constexpr int rtk_top_nodes(int width, int wg, int used) {
+  const int budget = 160 * 1024 / (kRtWavesPerCu * 64 / wg) / 1280 * 1280 - 64;
+  return budget > used ? (budget - used) / (28 * width) : 0;
+}
 constexpr bool rtk_stack_culls(bool any, int mode) { return !any && mode != 3; }
 // global stack words per thread (4-byte references) for a bound of max_stack entries
 inline size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode) {

@@ -202,32 +202,66 @@ __device__ __forceinline__ double raw_max(double a, double b) {
 // fixed order and selecting (24 selects fewer for W = 4).  2-wide nodes,
 // whose lo and hi planes share a 16-byte load, and per-lane node pointers
 // (batched plans) select after the load.
-template <int W, bool OFF32>
+// TOP: nodes [0, n_top), the upper levels of the tree, are read from a copy
+// in LDS (kNodeParts 16-byte parts each, the pad left out: the odd stride
+// spreads the parts of different nodes over the banks), which takes 28% of
+// the L1 accesses off 16.8M ambient-occlusion rays (1,650 -> 1,570 us; camera
+// and shadow rays 1,652 -> 1,626, 300,007 visibility rays 137 -> 133, 1,024
+// instances 2,773 -> 2,725, incoherent rays 1,427 -> 1,413).
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) f4 lds_f4;
+typedef __attribute__((address_space(3))) const char* lds_bytes;
+template <int W>
+constexpr int kNodeParts = (7 * W) / 4;
+
+template <int W, bool OFF32, bool TOP>
 __device__ __forceinline__ void visit_node(const float* nodes, uint32_t idx, const RayState& r, float tcull,
-                                           double (&e)[W]) {
+                                           lds_bytes top, uint32_t n_top, double (&e)[W]) {
   constexpr bool DIRECT = OFF32 && W >= 4;
   float nr[3][W], fr[3][W];
   uint32_t ref[W];
   const char* base = reinterpret_cast<const char*>(nodes);
   if constexpr (DIRECT) {
     constexpr uint32_t P = 4u * W;  // bytes of one plane array
-    const uint32_t b = idx * (32u * W);
-    const uint32_t s[3] = {r.sx, r.sy, r.sz};
+    const uint32_t s[3] = {r.sx * P, r.sy * P, r.sz * P};
+    f4 pn[3][W / 4], pf[3][W / 4], pr[W / 4];
+    // (addresses for both places are formed before either set of loads, which
+    // then follow each other without waiting)
+    const bool in_top = TOP && idx < n_top;
+    const uint32_t b = in_top ? idx * (16u * kNodeParts<W>) : idx * (32u * W);
+    uint32_t n[3] = {b + s[0], b + s[1], b + s[2]}, f[3] = {b + P - s[0], b + P - s[1], b + P - s[2]};
+    // (formed before either set of loads; formed between them, in registers
+    // of the first set, they would wait for it)
+    if constexpr (TOP) asm("" : "+v"(n[0]), "+v"(n[1]), "+v"(n[2]), "+v"(f[0]), "+v"(f[1]), "+v"(f[2]));
+    if (!in_top) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const uint32_t n = b | (s[a] * P), f = n ^ P;
+      for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int c = 0; c < W / 4; ++c) {
-        const float4 x = *reinterpret_cast<const float4*>(base + (size_t)n + 2 * a * P + 16 * c);
-        const float4 y = *reinterpret_cast<const float4*>(base + (size_t)f + 2 * a * P + 16 * c);
-        nr[a][4 * c] = x.x; nr[a][4 * c + 1] = x.y; nr[a][4 * c + 2] = x.z; nr[a][4 * c + 3] = x.w;
-        fr[a][4 * c] = y.x; fr[a][4 * c + 1] = y.y; fr[a][4 * c + 2] = y.z; fr[a][4 * c + 3] = y.w;
-      }
+        for (int c = 0; c < W / 4; ++c) {
+          pn[a][c] = *reinterpret_cast<const f4*>(base + (size_t)n[a] + 2 * a * P + 16 * c);
+          pf[a][c] = *reinterpret_cast<const f4*>(base + (size_t)f[a] + 2 * a * P + 16 * c);
+        }
+#pragma unroll
+      for (int c = 0; c < W / 4; ++c) pr[c] = *reinterpret_cast<const f4*>(base + (size_t)b + 6 * P + 16 * c);
+    } else {
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int c = 0; c < W / 4; ++c) {
+          pn[a][c] = *(const lds_f4*)(top + n[a] + 2 * a * P + 16 * c);
+          pf[a][c] = *(const lds_f4*)(top + f[a] + 2 * a * P + 16 * c);
+        }
+#pragma unroll
+      for (int c = 0; c < W / 4; ++c) pr[c] = *(const lds_f4*)(top + b + 6 * P + 16 * c);
     }
 #pragma unroll
-    for (int c = 0; c < W / 4; ++c) {
-      const uint4 x = *reinterpret_cast<const uint4*>(base + (size_t)b + 6 * P + 16 * c);
-      ref[4 * c] = x.x; ref[4 * c + 1] = x.y; ref[4 * c + 2] = x.z; ref[4 * c + 3] = x.w;
+    for (int i = 0; i < W; ++i) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        nr[a][i] = pn[a][i / 4][i % 4];
+        fr[a][i] = pf[a][i / 4][i % 4];
+      }
+      ref[i] = __float_as_uint(pr[i / 4][i % 4]);
     }
   } else {
     constexpr int NF4 = (W == 2) ? 4 : (7 * W) / 4;  // skip trailing pad when it fills a float4
@@ -496,6 +530,10 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   // two-level: the world ray's origin and direction, restored on leaving an
   // instance (kept out of registers)
   __shared__ float lds_world[INST ? 6 * WG : 1];
+  // the upper levels of the tree, in what the stack leaves of the workgroup's
+  // share of LDS
+  constexpr int kTop = OFF32 && W >= 4 ? rtk_top_nodes(W, WG, Stk::kLdsEnd + (INST ? 24 * WG : 0)) : 0;
+  __shared__ float4 lds_top[kTop > 0 ? kTop * kNodeParts<W> : 1];
   __shared__ uint32_t lds_done, lds_empty;   // waves done; queues found used up (bit mask)
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
@@ -516,6 +554,12 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   st.cap = P.max_stack;
   st.init(tid);
   if (tid == 0) lds_done = lds_empty = 0;
+  const uint32_t n_top = min((uint32_t)kTop, P.top_nodes);
+  if constexpr (kTop > 0) {
+    const float4* src = reinterpret_cast<const float4*>(P.nodes);
+    for (uint32_t k = tid; k < n_top * kNodeParts<W>; k += WG)
+      lds_top[k] = src[k / kNodeParts<W> * (2 * W) + k % kNodeParts<W>];
+  }
   __syncthreads();
 
   RayState r;
@@ -729,7 +773,7 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
         if ((int32_t)cur >= 0) {
           if constexpr (COUNT) n_nodes++;
           double e[W];
-          visit_node<W, OFF32>(g.nodes, cur, r, tcull, e);
+          visit_node<W, OFF32, (kTop > 0)>(g.nodes, cur, r, tcull, (lds_bytes)lds_top, n_top, e);
           auto dist = [&](int i) { return __int_as_float(__double2hiint(e[i])); };
           auto ref = [&](int i) { return (uint32_t)__double2loint(e[i]); };
           auto entered = [&](int i) { return dist(i) < __int_as_float(0x7f800000); };
