@@ -14,9 +14,9 @@
 //      finds, among the kPlocRadius clusters on either side, the one whose
 //      merged box has the least surface area; mutual nearest neighbours are
 //      merged into a new node; the list is compacted; repeat.  One pass is
-//      four launches (neighbours, merge flags, an exclusive scan that
-//      numbers the new nodes, merge + compaction), so the tree is the same
-//      on every run;
+//      three launches (neighbours, pairs per tile, merge + compaction), and
+//      the passes below 1,024 clusters are one launch of one workgroup; new
+//      nodes are numbered by position, so the tree is the same on every run;
 //   7. the binary tree collapsed into W-wide nodes level by level (the
 //      widest-child expansion of the host builder), leaves holding subtrees
 //      of at most max_leaf triangles; each subtree gets a contiguous range of
@@ -166,10 +166,20 @@ __global__ void morton_kernel(const float4* centre, const uint32_t* ids, uint32_
 // 20.6 / 21.3 / 20.4 / 20.8 node visits per incoherent ray; 32 is kept.
 constexpr int kPlocRadius = 32;
 
+// Where a pass stands: the n clusters are list `side`; `made` merges have
+// been done; `force` is set after a pass without a mutual pair (possible only
+// through exact ties of both area and hash), and then (2k, 2k + 1) are paired.
+// Pass p reads entry p and writes entry p + 1, so the passes of a batch are
+// launched without the host between them.
+struct PlocState {
+  uint32_t n, made, force, side;
+};
+
 __global__ void leaf_boxes_kernel(const float* V, const uint32_t* I, const uint32_t* sorted_ids, uint32_t m,
-                                  float* box, uint32_t* count, uint32_t* clusters) {
+                                  float* box, uint32_t* count, uint32_t* clusters, PlocState* state) {
   uint32_t k = blockIdx.x * 256u + threadIdx.x;
   if (k >= m) return;
+  if (k == 0u) state[0] = PlocState{m, 0u, 0u, 0u};
   float p[3][3];
   load_tri(V, I, sorted_ids[k], p);
   uint32_t id = m - 1u + k;
@@ -195,52 +205,91 @@ __device__ __forceinline__ uint32_t pair_hash(uint32_t a, uint32_t b) {
   return h;
 }
 
+// A better neighbour by (area bits, pair hash, position): a pair's order is
+// the same from either side, so mutual neighbours are well defined.  The hash
+// is five quarter-rate multiplies and settles ties only, so it is computed
+// only for those.
+__device__ __forceinline__ uint32_t tie_hash(uint32_t i, uint32_t j) { return pair_hash(min(i, j), max(i, j)); }
+__device__ __forceinline__ void ploc_take(uint32_t i, uint32_t j, uint32_t bits, uint32_t& best, uint32_t& arg) {
+  if (bits == best && tie_hash(i, j) < tie_hash(i, arg)) arg = j;
+  if (bits < best) {
+    best = bits;
+    arg = j;
+  }
+}
+
+// Half surface area of the box around two boxes (rows of lo xyz, hi xyz), as
+// bits: it is >= 0, because boxes are finite and not inverted.
+template <int T>
+__device__ __forceinline__ uint32_t merged_area(const float (&mine)[6], const float (*sb)[T], int l) {
+  float dx = fmaxf(mine[3], sb[3][l]) - fminf(mine[0], sb[0][l]);
+  float dy = fmaxf(mine[4], sb[4][l]) - fminf(mine[1], sb[1][l]);
+  float dz = fmaxf(mine[5], sb[5][l]) - fminf(mine[2], sb[2][l]);
+  return __float_as_uint(dx * dy + dy * dz + dz * dx);
+}
+
+struct PlocParams {
+  PlocState* state;    // kPlocBatch + 1 entries
+  uint32_t* list[2];   // cluster ids in Morton order
+  uint32_t* nn;        // nearest neighbour of each position
+  uint2* sums;         // per kPlocTile positions: lower and upper halves of pairs
+  uint32_t *left, *right, *count;
+  float* box;
+  uint32_t m;
+};
+
+// The multi-block passes stop at kPlocTail clusters, where one workgroup
+// finishes the tree out of LDS.  A pass is three launches of a few
+// microseconds each whatever its size, and a pass of 1,024 clusters takes one
+// compute unit about as long; below that it only gets cheaper (33 of the 55
+// passes over an 81,920-triangle mesh have 2,048 clusters or fewer).
+// Clustering with seven launches, a copy and a synchronisation a pass took a
+// build of that mesh 4.4 ms, and 2.9 ms for 5,120 triangles; this way the
+// builds take 1.5 and 0.8 ms.
+constexpr uint32_t kPlocTail = 1024;
+constexpr uint32_t kPlocTile = 1024;
+// Passes per host synchronisation.  A synchronisation leaves the GPU idle for
+// about 40 us, a pass that finds nothing left to do takes about 5 us.
+constexpr int kPlocBatch = 8;
+
 // nn[i] = the cluster among positions [i - r, i + r] whose merged box with i
-// has the least half surface area (ties: the pair hash).  A pair's key is
-// the same computed from either side, so mutual neighbours are well defined.
-__global__ __launch_bounds__(256) void ploc_nn_kernel(const uint32_t* clusters, uint32_t n, const float* box,
-                                                     uint32_t* nn) {
+// has the least half surface area (ties: the pair hash).
+__global__ __launch_bounds__(256) void ploc_nn_kernel(PlocParams P, int pass) {
   constexpr int T = 256 + 2 * kPlocRadius;
   __shared__ float sb[6][T];
+  const PlocState st = P.state[pass];
+  const int n = (int)st.n;
   const int base = (int)(blockIdx.x * 256u) - kPlocRadius;
+  if (st.n <= kPlocTail || st.force || base + kPlocRadius >= n) return;
+  const uint32_t* clusters = P.list[st.side];
   for (int t = threadIdx.x; t < T; t += 256) {
     int i = base + t;
-    if (i >= 0 && i < (int)n) {
-      const float* q = box + 6 * (size_t)clusters[i];
+    if (i >= 0 && i < n) {
+      const float* q = P.box + 6 * (size_t)clusters[i];
 #pragma unroll
       for (int a = 0; a < 6; ++a) sb[a][t] = q[a];
     }
   }
   __syncthreads();
-  const int i = (int)(blockIdx.x * 256u + threadIdx.x);
-  if (i >= (int)n) return;
+  const int i = base + kPlocRadius + (int)threadIdx.x;
+  if (i >= n) return;
   const int li = i - base;
-  const float lx = sb[0][li], ly = sb[1][li], lz = sb[2][li];
-  const float hx = sb[3][li], hy = sb[4][li], hz = sb[5][li];
-  uint64_t best = ~0ull;
-  uint32_t arg = (uint32_t)i;
-  const int jlo = max(i - kPlocRadius, 0), jhi = min(i + kPlocRadius, (int)n - 1);
-  for (int j = jlo; j <= jhi; ++j) {
-    if (j == i) continue;
-    const int lj = j - base;
-    float dx = fmaxf(hx, sb[3][lj]) - fminf(lx, sb[0][lj]);
-    float dy = fmaxf(hy, sb[4][lj]) - fminf(ly, sb[1][lj]);
-    float dz = fmaxf(hz, sb[5][lj]) - fminf(lz, sb[2][lj]);
-    float area = dx * dy + dy * dz + dz * dx;  // >= 0: boxes are finite and not inverted
-    uint32_t lo = (uint32_t)min(i, j), hi = (uint32_t)max(i, j);
-    uint64_t key = ((uint64_t)__float_as_uint(area) << 32) | pair_hash(lo, hi);
-    if (key < best) {
-      best = key;
-      arg = (uint32_t)j;
-    }
-  }
-  nn[i] = arg;
+  float mine[6];
+#pragma unroll
+  for (int a = 0; a < 6; ++a) mine[a] = sb[a][li];
+  uint32_t best = 0xFFFFFFFFu, arg = (uint32_t)i;
+  const int jlo = max(i - kPlocRadius, 0), jhi = min(i + kPlocRadius, n - 1);
+#pragma unroll 4
+  for (int j = jlo; j < i; ++j) ploc_take((uint32_t)i, (uint32_t)j, merged_area<T>(mine, sb, j - base), best, arg);
+#pragma unroll 4
+  for (int j = i + 1; j <= jhi; ++j) ploc_take((uint32_t)i, (uint32_t)j, merged_area<T>(mine, sb, j - base), best, arg);
+  P.nn[i] = arg;
 }
 
 // The partner of position i in this pass: its nearest neighbour when the
-// relation is mutual (or, in a pass forced to pair (2k, 2k+1) because the
-// previous pass found no mutual pair, its even/odd partner); n if none.
-__device__ __forceinline__ uint32_t ploc_partner(const uint32_t* nn, uint32_t n, int force, uint32_t i) {
+// relation is mutual (in a forced pass its even/odd partner); n if none.
+template <typename N>
+__device__ __forceinline__ uint32_t ploc_partner(const N* nn, uint32_t n, uint32_t force, uint32_t i) {
   if (force) {
     uint32_t j = i ^ 1u;
     return j < n ? j : n;
@@ -249,43 +298,196 @@ __device__ __forceinline__ uint32_t ploc_partner(const uint32_t* nn, uint32_t n,
   return (j < n && j != i && nn[j] == i) ? j : n;
 }
 
-__global__ void ploc_flag_kernel(const uint32_t* nn, uint32_t n, int force, uint32_t* flag) {
-  uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n) return;
-  uint32_t j = ploc_partner(nn, n, force, i);
-  flag[i] = (j < n && i < j) ? 1u : 0u;
+// Sums of (lower, upper) over the block's threads before this one, and over
+// all of them.  `part` is LDS for 16 waves; a barrier is passed before it is
+// written and one after.
+__device__ __forceinline__ void pair_scan(bool lower, bool upper, uint2* part, uint2& before, uint2& all) {
+  const uint64_t bl = __ballot(lower), bu = __ballot(upper);
+  const uint64_t below = (1ull << (threadIdx.x & 63u)) - 1ull;
+  const uint32_t wave = threadIdx.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63u) == 0u) part[wave] = make_uint2((uint32_t)__popcll(bl), (uint32_t)__popcll(bu));
+  __syncthreads();
+  before = make_uint2((uint32_t)__popcll(bl & below), (uint32_t)__popcll(bu & below));
+  all = make_uint2(0u, 0u);
+#pragma unroll
+  for (uint32_t w = 0; w < 16u; ++w) {
+    const uint2 p = part[w];
+    if (w < wave) {
+      before.x += p.x;
+      before.y += p.y;
+    }
+    all.x += p.x;
+    all.y += p.y;
+  }
 }
 
-// The lower position of a merged pair makes node top - off[i] and keeps its
-// place in the list; the higher one is dropped (keep = 0).
-__global__ void ploc_merge_kernel(const uint32_t* clusters, const uint32_t* nn, uint32_t n, int force,
-                                  const uint32_t* off, uint32_t top, uint32_t* left, uint32_t* right,
-                                  uint32_t* count, float* box, uint32_t* out, uint8_t* keep) {
-  uint32_t i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n) return;
-  uint32_t j = ploc_partner(nn, n, force, i);
-  uint32_t ci = clusters[i];
-  if (j >= n) {
-    out[i] = ci;
-    keep[i] = 1;
+// lower and upper halves of merged pairs in each tile of kPlocTile positions
+__global__ __launch_bounds__(1024) void ploc_count_kernel(PlocParams P, int pass) {
+  __shared__ uint2 part[16];
+  const PlocState st = P.state[pass];
+  if (st.n <= kPlocTail || blockIdx.x * kPlocTile >= st.n) return;
+  const uint32_t i = blockIdx.x * kPlocTile + threadIdx.x;
+  const uint32_t j = i < st.n ? ploc_partner(P.nn, st.n, st.force, i) : st.n;
+  uint2 before, all;
+  pair_scan(j < st.n && i < j, j < st.n && j < i, part, before, all);
+  if (threadIdx.x == 0) P.sums[blockIdx.x] = all;
+}
+
+// The lower position of a merged pair makes node m - 2 - (merges before it)
+// and keeps its place in the list; the upper one is dropped.  Every block adds
+// up the sums of the tiles before its own (8 bytes per 1,024 clusters), which
+// takes the place of a scan and a selection of their own.
+__global__ __launch_bounds__(1024) void ploc_merge_kernel(PlocParams P, int pass) {
+  __shared__ uint2 part[16];
+  __shared__ uint2 sum_before;
+  const PlocState st = P.state[pass];
+  if (st.n <= kPlocTail) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) P.state[pass + 1] = st;
     return;
   }
-  if (j < i) {
-    keep[i] = 0;
-    return;
+  if (blockIdx.x * kPlocTile >= st.n) return;
+  if (threadIdx.x == 0) sum_before = make_uint2(0u, 0u);
+  __syncthreads();
+  uint2 own = make_uint2(0u, 0u);
+  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 1024u) {
+    const uint2 p = P.sums[b];
+    own.x += p.x;
+    own.y += p.y;
   }
-  uint32_t cj = clusters[j];
-  uint32_t id = top - off[i];
-  left[id] = ci;
-  right[id] = cj;
-  count[id] = count[ci] + count[cj];
+  for (int o = 32; o > 0; o >>= 1) {
+    own.x += __shfl_down(own.x, o);
+    own.y += __shfl_down(own.y, o);
+  }
+  if ((threadIdx.x & 63u) == 0u && own.x + own.y != 0u) {
+    atomicAdd(&sum_before.x, own.x);
+    atomicAdd(&sum_before.y, own.y);
+  }
+  const uint32_t n = st.n, i = blockIdx.x * kPlocTile + threadIdx.x;
+  const uint32_t j = i < n ? ploc_partner(P.nn, n, st.force, i) : n;
+  const bool lower = j < n && i < j, upper = j < n && j < i;
+  uint2 before, all;
+  pair_scan(lower, upper, part, before, all);  // its barriers order sum_before as well
+  const uint2 tiles = sum_before;
+  const uint32_t* in = P.list[st.side];
+  uint32_t* out = P.list[st.side ^ 1u];
+  if (i < n && !upper) {
+    const uint32_t ci = in[i];
+    uint32_t id = ci;
+    if (lower) {
+      const uint32_t cj = in[j];
+      id = P.m - 2u - st.made - (tiles.x + before.x);
+      P.left[id] = ci;
+      P.right[id] = cj;
+      P.count[id] = P.count[ci] + P.count[cj];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    box[6 * (size_t)id + a] = fminf(box[6 * (size_t)ci + a], box[6 * (size_t)cj + a]);
-    box[6 * (size_t)id + 3 + a] = fmaxf(box[6 * (size_t)ci + 3 + a], box[6 * (size_t)cj + 3 + a]);
+      for (int a = 0; a < 3; ++a) {
+        P.box[6 * (size_t)id + a] = fminf(P.box[6 * (size_t)ci + a], P.box[6 * (size_t)cj + a]);
+        P.box[6 * (size_t)id + 3 + a] = fmaxf(P.box[6 * (size_t)ci + 3 + a], P.box[6 * (size_t)cj + 3 + a]);
+      }
+    }
+    out[i - (tiles.y + before.y)] = id;
   }
-  out[i] = id;
-  keep[i] = 1;
+  if (blockIdx.x == (n - 1u) / kPlocTile && threadIdx.x == 0) {
+    const uint32_t pairs = tiles.x + all.x;
+    P.state[pass + 1] = PlocState{n - pairs, st.made + pairs, pairs == 0u ? 1u : 0u, st.side ^ 1u};
+  }
+}
+
+// The last passes, at most kPlocTail clusters, in one workgroup with the boxes
+// in LDS.  Bound by the chain of passes: a search of 64 neighbours and four
+// barriers each.  The search of one cluster is spread over as many threads as
+// there are to spare (up to 32).
+__global__ __launch_bounds__(1024) void ploc_tail_kernel(PlocParams P, int pass) {
+  constexpr int T = (int)kPlocTail;
+  __shared__ float sb[6][T];
+  __shared__ uint32_t ids[T], cnt[T];
+  __shared__ uint16_t nn[T];
+  __shared__ uint2 part[16];
+  PlocState st = P.state[pass];
+  if (st.n > kPlocTail) {  // not there yet: the next batch goes on from entry 0
+    if (threadIdx.x == 0) P.state[0] = st;
+    return;
+  }
+  const uint32_t t = threadIdx.x;
+  if (t < st.n) {
+    const uint32_t c = P.list[st.side][t];
+    ids[t] = c;
+    cnt[t] = P.count[c];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) sb[a][t] = P.box[6 * (size_t)c + a];
+  }
+  __syncthreads();
+  while (st.n > 1u) {
+    const uint32_t n = st.n;
+    if (!st.force) {
+      uint32_t s = 0;
+      while (s < 5u && (n << (s + 1u)) <= 1024u) ++s;
+      const uint32_t i = t >> s;
+      uint32_t best = 0xFFFFFFFFu, arg = i;
+      if (i < n) {
+        float mine[6];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) mine[a] = sb[a][i];
+        const int lo = max((int)i - kPlocRadius, 0), hi = min((int)i + kPlocRadius, (int)n - 1);
+#pragma unroll 4
+        for (int j = lo + (int)(t & ((1u << s) - 1u)); j <= hi; j += 1 << s)
+          if (j != (int)i) ploc_take(i, (uint32_t)j, merged_area<T>(mine, sb, j), best, arg);
+      }
+      for (uint32_t o = 1u; o < (1u << s); o <<= 1) {
+        const uint32_t b2 = __shfl_xor(best, (int)o), a2 = __shfl_xor(arg, (int)o);
+        bool take = b2 < best;
+        if (b2 == best && a2 != arg) {  // a thread without a candidate has the position itself
+          const uint32_t h1 = tie_hash(i, arg), h2 = tie_hash(i, a2);
+          take = h2 < h1 || (h2 == h1 && a2 < arg);
+        }
+        if (take) {
+          best = b2;
+          arg = a2;
+        }
+      }
+      if (i < n && (t & ((1u << s) - 1u)) == 0u) nn[i] = (uint16_t)arg;
+    }
+    __syncthreads();
+    const uint32_t j = t < n ? ploc_partner(nn, n, st.force, t) : n;
+    const bool lower = j < n && t < j, upper = j < n && j < t;
+    uint32_t id = 0u, c = 0u;
+    float q[6];
+    uint2 before, all;
+    pair_scan(lower, upper, part, before, all);
+    if (t < n) {
+      id = ids[t];
+      c = cnt[t];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) q[a] = sb[a][t];
+      if (lower) {
+        const uint32_t made = P.m - 2u - st.made - before.x;
+        P.left[made] = id;
+        P.right[made] = ids[j];
+        c += cnt[j];
+        P.count[made] = c;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          q[a] = fminf(q[a], sb[a][j]);
+          q[3 + a] = fmaxf(q[3 + a], sb[3 + a][j]);
+        }
+#pragma unroll
+        for (int a = 0; a < 6; ++a) P.box[6 * (size_t)made + a] = q[a];
+        id = made;
+      }
+    }
+    __syncthreads();
+    if (t < n && !upper) {
+      const uint32_t to = t - before.y;
+      ids[to] = id;
+      cnt[to] = c;
+#pragma unroll
+      for (int a = 0; a < 6; ++a) sb[a][to] = q[a];
+    }
+    st = PlocState{n - all.x, st.made + all.x, all.x == 0u ? 1u : 0u, 0u};
+    __syncthreads();
+  }
+  if (t == 0) P.state[0] = st;
 }
 
 struct Item {
@@ -574,8 +776,9 @@ hipError_t build(const Input& in, Output& out, bool& index_error, hipStream_t s)
   // 6. PLOC
   const uint32_t nb = 2 * m - 1;
   uint32_t *left = nullptr, *right = nullptr, *count = nullptr, *perm = nullptr;
-  uint32_t *cl_a = nullptr, *cl_b = nullptr, *nn = nullptr, *flag = nullptr, *off = nullptr, *n_keep = nullptr;
-  uint8_t* keep_flag = nullptr;
+  uint32_t *cl_a = nullptr, *cl_b = nullptr, *nn = nullptr;
+  uint2* sums = nullptr;
+  PlocState* state = nullptr;
   float* box = nullptr;
   RTD_TRY(tmp.alloc(&left, m));
   RTD_TRY(tmp.alloc(&right, m));
@@ -584,45 +787,30 @@ hipError_t build(const Input& in, Output& out, bool& index_error, hipStream_t s)
   RTD_TRY(tmp.alloc(&cl_a, m));
   RTD_TRY(tmp.alloc(&cl_b, m));
   RTD_TRY(tmp.alloc(&nn, m));
-  RTD_TRY(tmp.alloc(&flag, m));
-  RTD_TRY(tmp.alloc(&off, m));
-  RTD_TRY(tmp.alloc(&n_keep, 1));
-  RTD_TRY(tmp.alloc(&keep_flag, m));
+  RTD_TRY(tmp.alloc(&sums, (m + kPlocTile - 1) / kPlocTile));
+  RTD_TRY(tmp.alloc(&state, kPlocBatch + 1));
   RTD_TRY(tmp.alloc(&box, (size_t)nb * 6));
   hipLaunchKernelGGL(leaf_boxes_kernel, dim3(blocks(m)), dim3(256), 0, s, out.vertices, out.indices, ids_sorted, m,
-                     box, count, cl_a);
+                     box, count, cl_a, state);
   RTD_TRY(hipGetLastError());
-  size_t scan_bytes = 0, sel_bytes = 0;
-  RTD_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, flag, off, (int)m, s));
-  RTD_TRY(hipcub::DeviceSelect::Flagged(nullptr, sel_bytes, cl_b, keep_flag, cl_a, n_keep, (int)m, s));
-  const size_t ploc_bytes = std::max(scan_bytes, sel_bytes);
-  void* ploc_tmp = nullptr;
-  RTD_TRY(tmp.alloc(reinterpret_cast<uint8_t**>(&ploc_tmp), ploc_bytes));
-  // the n clusters are cl_a[0, n); internal ids below `top` + 1 are still free
-  uint32_t n = m, made = 0;
-  int force = 0;
-  while (n > 1) {
-    const uint32_t top = m - 2 - made;  // id of this pass's first new node
-    if (!force) hipLaunchKernelGGL(ploc_nn_kernel, dim3(blocks(n)), dim3(256), 0, s, cl_a, n, box, nn);
-    hipLaunchKernelGGL(ploc_flag_kernel, dim3(blocks(n)), dim3(256), 0, s, nn, n, force, flag);
-    size_t b1 = ploc_bytes;
-    RTD_TRY(hipcub::DeviceScan::ExclusiveSum(ploc_tmp, b1, flag, off, (int)n, s));
-    hipLaunchKernelGGL(ploc_merge_kernel, dim3(blocks(n)), dim3(256), 0, s, cl_a, nn, n, force, off, top, left,
-                       right, count, box, cl_b, keep_flag);
-    size_t b2 = ploc_bytes;
-    RTD_TRY(hipcub::DeviceSelect::Flagged(ploc_tmp, b2, cl_b, keep_flag, cl_a, n_keep, (int)n, s));
+  const PlocParams ploc{state, {cl_a, cl_b}, nn, sums, left, right, count, box, m};
+  for (PlocState st{m, 0u, 0u, 0u};;) {
+    const uint32_t tiles = (st.n + kPlocTile - 1) / kPlocTile;
+    const int passes = st.n > kPlocTail ? kPlocBatch : 0;
+    for (int p = 0; p < passes; ++p) {
+      hipLaunchKernelGGL(ploc_nn_kernel, dim3(blocks(st.n)), dim3(256), 0, s, ploc, p);
+      hipLaunchKernelGGL(ploc_count_kernel, dim3(tiles), dim3(1024), 0, s, ploc, p);
+      hipLaunchKernelGGL(ploc_merge_kernel, dim3(tiles), dim3(1024), 0, s, ploc, p);
+    }
+    hipLaunchKernelGGL(ploc_tail_kernel, dim3(1), dim3(1024), 0, s, ploc, passes);
     RTD_TRY(hipGetLastError());
-    uint32_t n_new = n;
-    RTD_TRY(hipMemcpyAsync(&n_new, n_keep, 4, hipMemcpyDeviceToHost, s));
+    const uint32_t n_old = st.n;
+    RTD_TRY(hipMemcpyAsync(&st, state, sizeof(st), hipMemcpyDeviceToHost, s));
     RTD_TRY(hipStreamSynchronize(s));
-    if (n_new > n) return hipErrorUnknown;  // cannot happen
-    made += n - n_new;
-    // a pass without a mutual pair (possible only through exact ties of both
-    // area and hash) is followed by one that pairs (2k, 2k + 1)
-    force = (n_new == n) ? 1 : 0;
-    n = n_new;
+    if (st.n == 1 && st.made == m - 1) break;  // m - 1 merges made ids m - 2 .. 0
+    // cannot happen: a pass merges, or else the forced pass after it does
+    if (st.n <= kPlocTail || st.n >= n_old) return hipErrorUnknown;
   }
-  if (made != m - 1) return hipErrorUnknown;  // m - 1 merges made ids m - 2 .. 0
   // 7. collapse, level by level; wide nodes of one level are numbered
   // consecutively, so the levels are index ranges
   const size_t fpn = 8 * (size_t)W;
