@@ -110,6 +110,19 @@ def test_ao_full_size_sampled(gpu, orc):
     acc.close()
 
 
+@pytest.mark.parametrize("width, height, samples", [(2, 2, 1), (23, 29, 1), (13, 7, 3), (13, 7, 511), (13, 7, 512),
+                                                    (13, 7, 513)])
+def test_ao_workgroup_edges(gpu, orc, width, height, samples):
+    """A workgroup of the AO-ray kernel takes 512 samples: a few rays of one
+    sample, 512 and a ragged rest, rays that straddle workgroups, a ray
+    a workgroup, and a ray longer than one."""
+    W = wl.ao_terrain(width, height, samples, k=335, nq=16)
+    acc, (ao, h, ar, occ) = _run(gpu, W)
+    S = orc.OracleScene.from_scene(W.scene)
+    _check_pixels(orc, W, S, np.arange(width * height), h, ar, occ, ao, f"ao {width}x{height}x{samples}")
+    acc.close()
+
+
 def test_ao_errors(gpu):
     torch, api, ctx = gpu
     from paper_2603_00292_amd import _capi
