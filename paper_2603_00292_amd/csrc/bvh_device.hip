@@ -13,7 +13,7 @@
 //      finds, among the kPlocRadius clusters on either side, the one whose
 //      merged box has the least surface area; mutual nearest neighbours are
 //      merged into a new node; the list is compacted; repeat.  One pass is
-//      three launches (neighbours, pairs per tile, merge + compaction), and
+//      two launches (pairs, merge + compaction), and
 //      the passes below 1,024 clusters are one launch of one workgroup; new
 //      nodes are numbered by position, so the tree is the same on every run;
 //   6. the binary tree collapsed into W-wide nodes level by level (the
@@ -27,6 +27,7 @@
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
+#include <cmath>
 
 namespace rtd {
 namespace {
@@ -241,80 +242,55 @@ __device__ __forceinline__ uint32_t merged_area(const float (&mine)[6], const fl
   return __float_as_uint(dx * dy + dy * dz + dz * dx);
 }
 
+// The best of `width` threads (a power of two, up to 64) that searched for i.
+__device__ __forceinline__ void ploc_best(uint32_t i, uint32_t width, uint32_t& best, uint32_t& arg) {
+  for (uint32_t o = 1u; o < width; o <<= 1) {
+    const uint32_t b2 = __shfl_xor(best, (int)o), a2 = __shfl_xor(arg, (int)o);
+    bool take = b2 < best;
+    if (b2 == best && a2 != arg) {  // a thread without a candidate has the position itself
+      const uint32_t h1 = tie_hash(i, arg), h2 = tie_hash(i, a2);
+      take = h2 < h1 || (h2 == h1 && a2 < arg);
+    }
+    if (take) {
+      best = b2;
+      arg = a2;
+    }
+  }
+}
+
 struct PlocParams {
   PlocState* state;    // kPlocBatch + 1 entries
   uint32_t* list[2];   // cluster ids in Morton order
-  uint32_t* nn;        // nearest neighbour of each position
-  uint2* sums;         // per kPlocTile positions: lower and upper halves of pairs
+  uint32_t* partner;   // of each position in this pass: the other half of its pair, n if none
+  uint2* sums;         // per tile of the pair kernel: lower and upper halves of pairs
   uint32_t *left, *right, *count;
   float* box;
   uint32_t m;
 };
 
 // The multi-block passes stop at kPlocTail clusters, where one workgroup
-// finishes the tree out of LDS.  A pass is three launches of a few
-// microseconds each whatever its size, and a pass of 1,024 clusters takes one
-// compute unit about as long; below that it only gets cheaper (33 of the 55
-// passes over a 327,680-triangle mesh have 2,048 clusters or fewer).
-// Clustering with seven launches, a copy and a synchronisation a pass took a
-// build of that mesh 8.0 ms, and 2.9 ms for 5,120 triangles; this way the
-// builds took 4.0 and 0.84 ms.
+// finishes the tree out of LDS.  A pass is two launches of a few microseconds
+// each whatever its size, and a pass of 1,024 clusters takes one compute unit
+// about as long; below that it only gets cheaper (33 of the 55 passes over a
+// 327,680-triangle mesh have 2,048 clusters or fewer).
 constexpr uint32_t kPlocTail = 1024;
-constexpr uint32_t kPlocTile = 1024;
-// Passes per host synchronisation.  A synchronisation leaves the GPU idle for
-// about 40 us, a pass that finds nothing left to do takes about 5 us.
-constexpr int kPlocBatch = 8;
-
-// nn[i] = the cluster among positions [i - r, i + r] whose merged box with i
-// has the least half surface area (ties: the pair hash).
-__global__ __launch_bounds__(256) void ploc_nn_kernel(PlocParams P, int pass) {
-  constexpr int T = 256 + 2 * kPlocRadius;
-  __shared__ float sb[6][T];
-  const PlocState st = P.state[pass];
-  const int n = (int)st.n;
-  const int base = (int)(blockIdx.x * 256u) - kPlocRadius;
-  if (st.n <= kPlocTail || st.force || base + kPlocRadius >= n) return;
-  const uint32_t* clusters = P.list[st.side];
-  for (int t = threadIdx.x; t < T; t += 256) {
-    int i = base + t;
-    if (i >= 0 && i < n) {
-      const float* q = P.box + 6 * (size_t)clusters[i];
-#pragma unroll
-      for (int a = 0; a < 6; ++a) sb[a][t] = q[a];
-    }
-  }
-  __syncthreads();
-  const int i = base + kPlocRadius + (int)threadIdx.x;
-  if (i >= n) return;
-  const int li = i - base;
-  float mine[6];
-#pragma unroll
-  for (int a = 0; a < 6; ++a) mine[a] = sb[a][li];
-  uint32_t best = 0xFFFFFFFFu, arg = (uint32_t)i;
-  const int jlo = max(i - kPlocRadius, 0), jhi = min(i + kPlocRadius, n - 1);
-#pragma unroll 4
-  for (int j = jlo; j < i; ++j) ploc_take((uint32_t)i, (uint32_t)j, merged_area<T>(mine, sb, j - base), best, arg);
-#pragma unroll 4
-  for (int j = i + 1; j <= jhi; ++j) ploc_take((uint32_t)i, (uint32_t)j, merged_area<T>(mine, sb, j - base), best, arg);
-  P.nn[i] = arg;
-}
-
-// The partner of position i in this pass: its nearest neighbour when the
-// relation is mutual (in a forced pass its even/odd partner); n if none.
-template <typename N>
-__device__ __forceinline__ uint32_t ploc_partner(const N* nn, uint32_t n, uint32_t force, uint32_t i) {
-  if (force) {
-    uint32_t j = i ^ 1u;
-    return j < n ? j : n;
-  }
-  uint32_t j = nn[i];
-  return (j < n && j != i && nn[j] == i) ? j : n;
-}
+// Positions per workgroup of the merge kernel; a multiple of the pair
+// kernel's tiles and even, so that the pairs of a forced pass stay in one.
+constexpr uint32_t kPlocTile = 960;
+constexpr uint32_t kPlocLarge = 1024 - 2 * kPlocRadius, kPlocSmall = 256 - 2 * kPlocRadius;
+// A host synchronisation leaves the GPU idle for about 40 us, a pass that
+// finds nothing left to do takes about 5 us.  A pass leaves about four fifths
+// of its clusters (22 passes from 327,680 to 2,048), so as many passes are
+// queued as that takes to reach kPlocTail; at least two, so that a pass without
+// a pair and the forced one after it are in one batch and the count shrinks.
+constexpr int kPlocBatch = 32;
+constexpr float kPlocDecay = 0.23f;
 
 // Sums of (lower, upper) over the block's threads before this one, and over
-// all of them.  `part` is LDS for 16 waves; a barrier is passed before it is
-// written and one after.
-__device__ __forceinline__ void pair_scan(bool lower, bool upper, uint2* part, uint2& before, uint2& all) {
+// all of them.  `part` is LDS for the block's waves; a barrier is passed
+// before it is written and one after.
+template <uint32_t WAVES>
+__device__ __forceinline__ void pair_scan(bool lower, bool upper, uint2 (&part)[WAVES], uint2& before, uint2& all) {
   const uint64_t bl = __ballot(lower), bu = __ballot(upper);
   const uint64_t below = (1ull << (threadIdx.x & 63u)) - 1ull;
   const uint32_t wave = threadIdx.x >> 6;
@@ -324,7 +300,7 @@ __device__ __forceinline__ void pair_scan(bool lower, bool upper, uint2* part, u
   before = make_uint2((uint32_t)__popcll(bl & below), (uint32_t)__popcll(bu & below));
   all = make_uint2(0u, 0u);
 #pragma unroll
-  for (uint32_t w = 0; w < 16u; ++w) {
+  for (uint32_t w = 0; w < WAVES; ++w) {
     const uint2 p = part[w];
     if (w < wave) {
       before.x += p.x;
@@ -335,13 +311,74 @@ __device__ __forceinline__ void pair_scan(bool lower, bool upper, uint2* part, u
   }
 }
 
-// lower and upper halves of merged pairs in each tile of kPlocTile positions
-__global__ __launch_bounds__(1024) void ploc_count_kernel(PlocParams P, int pass) {
-  __shared__ uint2 part[16];
+// The partner of position i in this pass: its nearest neighbour when the
+// relation is mutual (in a forced pass its even/odd partner); n if none.
+// `nn` holds the neighbours of the positions from `first` on.
+template <typename N>
+__device__ __forceinline__ uint32_t ploc_partner(const N* nn, int first, uint32_t n, uint32_t force, uint32_t i) {
+  if (force) {
+    uint32_t j = i ^ 1u;
+    return j < n ? j : n;
+  }
+  const uint32_t j = nn[(int)i - first];
+  return (j != i && nn[(int)j - first] == i) ? j : n;
+}
+
+// The pairs of a pass.  The nearest neighbour of position i is the cluster
+// among [i - r, i + r] whose merged box with i has the least half surface area
+// (ties: the pair hash).  A tile of T - 2r positions also finds the neighbours
+// of the r positions on either side, so that it settles its own pairs and
+// counts them without another launch (3.8 us and a gap, and a pass over 20,000
+// clusters took 12).  Large passes are bound by the searches: T = 1,024 makes
+// 7% more of them.  Small ones are bound by the chain of 64 boxes a search, and
+// the chip has threads to spare: T = 256, which makes a third more, and four
+// threads a search (11.0 -> 7.3 us a pass).  All passes over a 327,680-triangle
+// mesh, kernels only: 714 us with a launch for the neighbours and one to count
+// the pairs, 550 us this way.
+template <int T, int S>
+__global__ __launch_bounds__(T * S) void ploc_pair_kernel(PlocParams P, int pass) {
+  constexpr int R = kPlocRadius, kBoxes = T + 2 * R, kIn = T - 2 * R;
+  static_assert(kPlocTile % kIn == 0 && kIn % 2 == 0, "tiles of the merge kernel");
+  __shared__ float sb[6][kBoxes];
+  __shared__ uint32_t nn[T];
+  __shared__ uint2 part[T * S / 64];
   const PlocState st = P.state[pass];
-  if (st.n <= kPlocTail || blockIdx.x * kPlocTile >= st.n) return;
-  const uint32_t i = blockIdx.x * kPlocTile + threadIdx.x;
-  const uint32_t j = i < st.n ? ploc_partner(P.nn, st.n, st.force, i) : st.n;
+  const int n = (int)st.n;
+  const int first = (int)(blockIdx.x * (uint32_t)kIn);
+  if (st.n <= kPlocTail || first >= n) return;
+  if (!st.force) {
+    const uint32_t* clusters = P.list[st.side];
+    const int base = first - 2 * R;  // position of sb[.][0]
+    for (int t = threadIdx.x; t < kBoxes; t += T * S) {
+      const int i = base + t;
+      if (i >= 0 && i < n) {
+        const float* q = P.box + 6 * (size_t)clusters[i];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) sb[a][t] = q[a];
+      }
+    }
+    __syncthreads();
+    const int i = first - R + (int)threadIdx.x / S;
+    uint32_t best = 0xFFFFFFFFu, arg = (uint32_t)i;
+    if (i >= 0 && i < n) {
+      float mine[6];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) mine[a] = sb[a][i - base];
+      const int jlo = max(i - R, 0), jhi = min(i + R, n - 1);
+#pragma unroll 4
+      for (int j = jlo + (int)threadIdx.x % S; j <= jhi; j += S)
+        if (j != i) ploc_take((uint32_t)i, (uint32_t)j, merged_area<kBoxes>(mine, sb, j - base), best, arg);
+    }
+    ploc_best((uint32_t)i, S, best, arg);
+    if ((int)threadIdx.x % S == 0) nn[threadIdx.x / S] = arg;  // (positions outside the list are not read)
+    __syncthreads();
+  }
+  const uint32_t i = (uint32_t)first + threadIdx.x;
+  uint32_t j = st.n;
+  if ((int)threadIdx.x < kIn && i < st.n) {
+    j = ploc_partner(nn, first - R, st.n, st.force, i);
+    P.partner[i] = j;
+  }
   uint2 before, all;
   pair_scan(j < st.n && i < j, j < st.n && j < i, part, before, all);
   if (threadIdx.x == 0) P.sums[blockIdx.x] = all;
@@ -349,9 +386,9 @@ __global__ __launch_bounds__(1024) void ploc_count_kernel(PlocParams P, int pass
 
 // The lower position of a merged pair makes node m - 2 - (merges before it)
 // and keeps its place in the list; the upper one is dropped.  Every block adds
-// up the sums of the tiles before its own (8 bytes per 1,024 clusters), which
-// takes the place of a scan and a selection of their own.
-__global__ __launch_bounds__(1024) void ploc_merge_kernel(PlocParams P, int pass) {
+// up the sums of the tiles before its own (`per` of the pair kernel's to one
+// of its own), which takes the place of a scan and a selection of their own.
+__global__ __launch_bounds__(1024) void ploc_merge_kernel(PlocParams P, int pass, uint32_t per) {
   __shared__ uint2 part[16];
   __shared__ uint2 sum_before;
   const PlocState st = P.state[pass];
@@ -363,7 +400,7 @@ __global__ __launch_bounds__(1024) void ploc_merge_kernel(PlocParams P, int pass
   if (threadIdx.x == 0) sum_before = make_uint2(0u, 0u);
   __syncthreads();
   uint2 own = make_uint2(0u, 0u);
-  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 1024u) {
+  for (uint32_t b = threadIdx.x; b < blockIdx.x * per; b += 1024u) {
     const uint2 p = P.sums[b];
     own.x += p.x;
     own.y += p.y;
@@ -377,14 +414,15 @@ __global__ __launch_bounds__(1024) void ploc_merge_kernel(PlocParams P, int pass
     atomicAdd(&sum_before.y, own.y);
   }
   const uint32_t n = st.n, i = blockIdx.x * kPlocTile + threadIdx.x;
-  const uint32_t j = i < n ? ploc_partner(P.nn, n, st.force, i) : n;
+  const bool mine = threadIdx.x < kPlocTile && i < n;
+  const uint32_t j = mine ? P.partner[i] : n;
   const bool lower = j < n && i < j, upper = j < n && j < i;
   uint2 before, all;
   pair_scan(lower, upper, part, before, all);  // its barriers order sum_before as well
   const uint2 tiles = sum_before;
   const uint32_t* in = P.list[st.side];
   uint32_t* out = P.list[st.side ^ 1u];
-  if (i < n && !upper) {
+  if (mine && !upper) {
     const uint32_t ci = in[i];
     uint32_t id = ci;
     if (lower) {
@@ -447,22 +485,11 @@ __global__ __launch_bounds__(1024) void ploc_tail_kernel(PlocParams P, int pass)
         for (int j = lo + (int)(t & ((1u << s) - 1u)); j <= hi; j += 1 << s)
           if (j != (int)i) ploc_take(i, (uint32_t)j, merged_area<T>(mine, sb, j), best, arg);
       }
-      for (uint32_t o = 1u; o < (1u << s); o <<= 1) {
-        const uint32_t b2 = __shfl_xor(best, (int)o), a2 = __shfl_xor(arg, (int)o);
-        bool take = b2 < best;
-        if (b2 == best && a2 != arg) {  // a thread without a candidate has the position itself
-          const uint32_t h1 = tie_hash(i, arg), h2 = tie_hash(i, a2);
-          take = h2 < h1 || (h2 == h1 && a2 < arg);
-        }
-        if (take) {
-          best = b2;
-          arg = a2;
-        }
-      }
+      ploc_best(i, 1u << s, best, arg);
       if (i < n && (t & ((1u << s) - 1u)) == 0u) nn[i] = (uint16_t)arg;
     }
     __syncthreads();
-    const uint32_t j = t < n ? ploc_partner(nn, n, st.force, t) : n;
+    const uint32_t j = t < n ? ploc_partner(nn, 0, n, st.force, t) : n;
     const bool lower = j < n && t < j, upper = j < n && j < t;
     uint32_t id = 0u, c = 0u;
     float q[6];
@@ -912,7 +939,7 @@ hipError_t build(const Input& in, Output& out, bool& index_error, hipStream_t s)
   uint32_t *keys = nullptr, *keys_sorted = nullptr, *ids_sorted = nullptr;
   uint8_t* sort_tmp = nullptr;
   uint32_t *left = nullptr, *right = nullptr, *count = nullptr, *perm = nullptr;
-  uint32_t *cl_a = nullptr, *cl_b = nullptr, *nn = nullptr;
+  uint32_t *cl_a = nullptr, *cl_b = nullptr, *partner = nullptr;
   uint2* sums = nullptr;
   PlocState* state = nullptr;
   float* box = nullptr;
@@ -929,8 +956,8 @@ hipError_t build(const Input& in, Output& out, bool& index_error, hipStream_t s)
   tmp.want(&perm, m);
   tmp.want(&cl_a, m);
   tmp.want(&cl_b, m);
-  tmp.want(&nn, m);
-  tmp.want(&sums, (m + kPlocTile - 1) / kPlocTile);
+  tmp.want(&partner, m);
+  tmp.want(&sums, (m + kPlocSmall - 1) / kPlocSmall);
   tmp.want(&state, kPlocBatch + 1);
   tmp.want(&box, (size_t)nb * 6);
   tmp.want(&P.nodes, (size_t)m * fpn);  // at most m wide nodes
@@ -944,14 +971,20 @@ hipError_t build(const Input& in, Output& out, bool& index_error, hipStream_t s)
   hipLaunchKernelGGL(leaf_boxes_kernel, dim3(blocks(m)), dim3(256), 0, s, out.vertices, out.indices, ids_sorted, m,
                      box, count, cl_a, state);
   RTD_TRY(hipGetLastError());
-  const PlocParams ploc{state, {cl_a, cl_b}, nn, sums, left, right, count, box, m};
+  const PlocParams ploc{state, {cl_a, cl_b}, partner, sums, left, right, count, box, m};
   for (PlocState st{m, 0u, 0u, 0u};;) {
     const uint32_t tiles = (st.n + kPlocTile - 1) / kPlocTile;
-    const int passes = st.n > kPlocTail ? kPlocBatch : 0;
+    const float to_tail = std::log((float)st.n / (float)kPlocTail) / kPlocDecay;
+    const int passes = st.n > kPlocTail ? std::min(std::max((int)std::ceil(to_tail), 2), kPlocBatch) : 0;
     for (int p = 0; p < passes; ++p) {
-      hipLaunchKernelGGL(ploc_nn_kernel, dim3(blocks(st.n)), dim3(256), 0, s, ploc, p);
-      hipLaunchKernelGGL(ploc_count_kernel, dim3(tiles), dim3(1024), 0, s, ploc, p);
-      hipLaunchKernelGGL(ploc_merge_kernel, dim3(tiles), dim3(1024), 0, s, ploc, p);
+      // (the kernels take any number of clusters; this one is by the number
+      // expected)
+      const bool large = (float)st.n * std::exp(-kPlocDecay * (float)p) > 65536.0f;
+      const uint32_t tile = large ? kPlocLarge : kPlocSmall;
+      const dim3 pair_grid((st.n + tile - 1) / tile);
+      if (large) hipLaunchKernelGGL((ploc_pair_kernel<1024, 1>), pair_grid, dim3(1024), 0, s, ploc, p);
+      else hipLaunchKernelGGL((ploc_pair_kernel<256, 4>), pair_grid, dim3(1024), 0, s, ploc, p);
+      hipLaunchKernelGGL(ploc_merge_kernel, dim3(tiles), dim3(1024), 0, s, ploc, p, kPlocTile / tile);
     }
     hipLaunchKernelGGL(ploc_tail_kernel, dim3(1), dim3(1024), 0, s, ploc, passes);
     RTD_TRY(hipGetLastError());
