@@ -180,25 +180,25 @@ struct Gather {
   uint32_t vertices = 0, triangles = 0, shift = 0, buckets = 0;
 };
 
-// Where a ray's key comes from: kind 0, its triangle (single level); 1, its
-// global triangle; 2, its instance.  Rays without a valid hit have no key.
+// Where a ray's key comes from: its triangle (single level), or its global
+// triangle and its instance (two-level: inst_ids is set).  Rays without a
+// valid hit have no key.
 struct KeySource {
   const uint32_t* hit_words;     // prim id at hit_words[4 i + 1]
   const uint32_t* inst_ids;      // two-level
   const uint2* inst_tris;        // two-level
   uint32_t inst_count;
   uint32_t triangles;            // single level
-  uint32_t kind;
 };
 
-__device__ __forceinline__ uint32_t ray_key(const KeySource& k, uint32_t i) {
+__device__ __forceinline__ uint32_t ray_key(const KeySource& k, uint32_t i, uint32_t& inst) {
   const uint32_t prim = k.hit_words[4 * (size_t)i + 1];
-  if (k.kind == 0) return prim < k.triangles ? prim : kNoKey;
-  const uint32_t inst = k.inst_ids[i];
+  inst = 0u;
+  if (!k.inst_ids) return prim < k.triangles ? prim : kNoKey;
+  inst = k.inst_ids[i];
   if (inst >= k.inst_count) return kNoKey;
   const uint2 it = k.inst_tris[inst];
-  if (prim >= it.y) return kNoKey;
-  return k.kind == 1 ? it.x + prim : inst;
+  return prim < it.y ? it.x + prim : kNoKey;
 }
 
 // Per context: buffers sized by the ray count (grown stream-ordered).
@@ -220,6 +220,13 @@ struct Bucketing {
   RayRec* rec;
 };
 
+// A histogram of rays over buckets, for its kernels (buckets == 0: none).
+struct Histogram {
+  uint32_t* counts;
+  uint32_t* totals;
+  uint32_t buckets, shift;
+};
+
 // Builds g from the mesh's indices (host copy): counting sort by vertex,
 // entries in ascending (triangle, corner) order.
 hipError_t gather_build(Gather& g, const uint32_t* host_indices, uint32_t vertices, uint32_t triangles);
@@ -237,10 +244,11 @@ hipError_t gather_tri_vertices(Gather& g, const uint32_t* indices, const float* 
 // frees and allocates stream-ordered on s (no device-wide synchronisation).
 hipError_t sort_reserve(SortBuf& b, uint32_t buckets, size_t n, hipStream_t s);
 void sort_release(SortBuf& b);
-// Histogram of the rays' keys (buckets of 2^shift keys) and its scans;
-// returns the adjoint kernel's placement.
-hipError_t bucket_rays(const KeySource& keys, uint32_t buckets, uint32_t shift, SortBuf& b, uint32_t n,
-                       hipStream_t s, Bucketing* out);
+// Histograms of the rays' keys and their scans, for the adjoint kernel's
+// placement: by triangle in b0 (buckets of 2^shift; NULL: not wanted) and, on
+// two-level accels, by instance in b1 (NULL: not wanted).
+hipError_t bucket_rays(const KeySource& keys, uint32_t n, hipStream_t s, SortBuf* b0, uint32_t buckets, uint32_t shift,
+                       Bucketing* out0, SortBuf* b1 = nullptr, uint32_t instances = 0, Bucketing* out1 = nullptr);
 // After the adjoint kernel placed the records: sum per corner and per
 // vertex, out[3 v + c] += the vertex sums.
 hipError_t gather_vertices(Gather& g, SortBuf& b, uint32_t n, float* out, hipStream_t s);

@@ -115,33 +115,52 @@ hipError_t convert(const Rows& r, uint32_t first, uint32_t count, int layout, in
 namespace rta {
 namespace {
 
-// per-tile histogram of the rays' buckets: counts[tile * buckets + bucket]
-// (bucket = key >> shift); rays without a key are not counted
-__global__ __launch_bounds__(1024) void hist_kernel(KeySource keys, uint32_t n, uint32_t shift, uint32_t buckets,
-                                                    uint32_t* counts) {
+// per-tile histograms of the rays' buckets: counts[tile * buckets + bucket]
+// (bucket = key >> shift); rays without a key are not counted.  Both groupings
+// of a two-level call are counted in one pass over the hits (bound by these
+// reads: 2,000,003 rays, 625 and 1,024 buckets, 12.2 us against 10.8 for each
+// pass; the column scans 6.5 against 6.4 each).
+__global__ __launch_bounds__(1024) void hist_kernel(KeySource keys, uint32_t n, Histogram H0, Histogram H1) {
   extern __shared__ uint32_t h[];
-  for (uint32_t b = threadIdx.x; b < buckets; b += 1024) h[b] = 0u;
+  uint32_t* h1 = h + H0.buckets;
+  for (uint32_t b = threadIdx.x; b < H0.buckets + H1.buckets; b += 1024) h[b] = 0u;
   __syncthreads();
-  uint32_t base = blockIdx.x * kTile;
-  uint32_t end = min(n, base + kTile);
-  for (uint32_t i = base + threadIdx.x; i < end; i += 1024) {
-    uint32_t k = ray_key(keys, i);
-    if (k != kNoKey) atomicAdd(&h[k >> shift], 1u);
+  constexpr uint32_t R = kTile / 1024;
+  const uint32_t base = blockIdx.x * kTile;
+  uint32_t key[R], inst[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = base + r * 1024 + threadIdx.x;
+    key[r] = kNoKey;
+    if (i < n) key[r] = ray_key(keys, i, inst[r]);
   }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (key[r] != kNoKey) {
+      if (H0.buckets) atomicAdd(&h[key[r] >> H0.shift], 1u);
+      if (H1.buckets) atomicAdd(&h1[inst[r]], 1u);
+    }
   __syncthreads();
-  uint32_t* row = counts + (size_t)blockIdx.x * buckets;
-  for (uint32_t b = threadIdx.x; b < buckets; b += 1024) row[b] = h[b];
+  uint32_t* row = H0.counts + (size_t)blockIdx.x * H0.buckets;
+  for (uint32_t b = threadIdx.x; b < H0.buckets; b += 1024) row[b] = h[b];
+  row = H1.counts + (size_t)blockIdx.x * H1.buckets;
+  for (uint32_t b = threadIdx.x; b < H1.buckets; b += 1024) row[b] = h1[b];
 }
 
 // Column scan: workgroup g owns buckets 64 g .. 64 g + 63 (one per lane) and
 // splits the tiles over its 16 waves; each bucket's tile counts become the
 // offsets of the tiles inside the bucket, and its total goes to totals[]
-// (the adjoint kernel scans the totals into bucket starts).
-__global__ __launch_bounds__(1024) void colscan_kernel(uint32_t* counts, uint32_t tiles, uint32_t buckets,
-                                                       uint32_t* totals) {
+// (the adjoint kernel scans the totals into bucket starts).  The workgroups of
+// the second histogram follow those of the first.
+__global__ __launch_bounds__(1024) void colscan_kernel(Histogram H0, Histogram H1, uint32_t tiles) {
   __shared__ uint32_t part[16][64];
   const uint32_t l = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t b = blockIdx.x * 64u + l;
+  const uint32_t groups0 = (H0.buckets + 63u) / 64u;
+  const bool second = blockIdx.x >= groups0;
+  uint32_t* counts = second ? H1.counts : H0.counts;
+  uint32_t* totals = second ? H1.totals : H0.totals;
+  const uint32_t buckets = second ? H1.buckets : H0.buckets;
+  const uint32_t b = (blockIdx.x - (second ? groups0 : 0u)) * 64u + l;
   const uint32_t per = (tiles + 15u) / 16u;
   const uint32_t t0 = min(tiles, w * per), t1 = min(tiles, t0 + per);
   // the loads of a block of kU tiles are issued together; the first block
@@ -549,22 +568,26 @@ void sort_release(SortBuf& b) {
   b = SortBuf();
 }
 
-hipError_t bucket_rays(const KeySource& keys, uint32_t buckets, uint32_t shift, SortBuf& b, uint32_t n,
-                       hipStream_t s, Bucketing* out) {
+static Histogram histogram(SortBuf& b, uint32_t buckets, uint32_t shift, uint32_t tiles, Bucketing* out) {
+  *out = Bucketing{b.counts, b.scan, b.scan + buckets, tiles, buckets, shift, b.rec};
+  return Histogram{b.counts, b.scan, buckets, shift};
+}
+
+hipError_t bucket_rays(const KeySource& keys, uint32_t n, hipStream_t s, SortBuf* b0, uint32_t buckets, uint32_t shift,
+                       Bucketing* out0, SortBuf* b1, uint32_t instances, Bucketing* out1) {
   uint32_t tiles = (n + kTile - 1) / kTile;
-  uint32_t* counts = b.counts;
-  uint32_t* totals = b.scan;
-  uint32_t* base = b.scan + buckets;
-  *out = Bucketing{counts, totals, base, tiles, buckets, shift, b.rec};
-  if (buckets == 0 || tiles == 0) return hipSuccess;   // no keys or no rays: no ray has a bucket
+  Histogram h0{}, h1{};
+  if (b0) h0 = histogram(*b0, buckets, shift, tiles, out0);
+  if (b1) h1 = histogram(*b1, instances, 0, tiles, out1);
+  const uint32_t groups = (h0.buckets + 63) / 64 + (h1.buckets + 63) / 64;
+  if (groups == 0 || tiles == 0) return hipSuccess;   // no keys or no rays: no ray has a bucket
   KeySource k = keys;
-  void* a1[] = {&k, &n, &shift, &buckets, &counts};
+  void* a1[] = {&k, &n, &h0, &h1};
   hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&hist_kernel), dim3(tiles), dim3(1024), a1,
-                                 buckets * sizeof(uint32_t), s);
+                                 (h0.buckets + h1.buckets) * sizeof(uint32_t), s);
   if (e != hipSuccess) return e;
-  void* a2[] = {&counts, &tiles, &buckets, &totals};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&colscan_kernel), dim3((buckets + 63) / 64), dim3(1024),
-                         a2, 0, s);
+  void* a2[] = {&h0, &h1, &tiles};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&colscan_kernel), dim3(groups), dim3(1024), a2, 0, s);
 }
 
 hipError_t gather_vertices(Gather& g, SortBuf& b, uint32_t n, float* out, hipStream_t s) {

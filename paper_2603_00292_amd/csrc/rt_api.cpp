@@ -1608,8 +1608,8 @@ rt_status rt_trace_backward(rt_accel accel, const rt_ray* rays, const rt_hit* hi
   p.n = n;
   p.d_origins = d_origins;
   p.d_directions = d_directions;
-  rta::KeySource keys{reinterpret_cast<const uint32_t*>(hits), nullptr, nullptr, 0, mesh.triangle_count, 0};
-  RT_HIP(rta::bucket_rays(keys, accel->gather.buckets, accel->gather.shift, ctx->sortbuf, n, s, &p.bk));
+  rta::KeySource keys{reinterpret_cast<const uint32_t*>(hits), nullptr, nullptr, 0, mesh.triangle_count};
+  RT_HIP(rta::bucket_rays(keys, n, s, &ctx->sortbuf, accel->gather.buckets, accel->gather.shift, &p.bk));
   RT_HIP(rtk_launch_backward(p, s));
   RT_HIP(rta::gather_vertices(accel->gather, ctx->sortbuf, n, d_vertices, s));
   RT_HIP(hipEventRecord(ctx->last_event, s));
@@ -1698,16 +1698,11 @@ rt_status rt_trace_backward_instances(rt_accel accel, const rt_ray* rays, const 
     }
     p.tri_vertices = g.tri_vertices;
     p.inst_tris = g.inst_tris;
-    rta::KeySource keys{reinterpret_cast<const uint32_t*>(hits), inst_ids, g.inst_tris, accel->instance_count, 0, 1};
-    if (p.want_vertices) {
-      RT_HIP(rta::sort_reserve(ctx->sortbuf, g.buckets, n, s));
-      RT_HIP(rta::bucket_rays(keys, g.buckets, g.shift, ctx->sortbuf, n, s, &p.vb));
-    }
-    if (p.want_frames) {
-      keys.kind = 2;
-      RT_HIP(rta::sort_reserve(ctx->sortbuf2, accel->instance_count, n, s));
-      RT_HIP(rta::bucket_rays(keys, accel->instance_count, 0, ctx->sortbuf2, n, s, &p.fb));
-    }
+    rta::KeySource keys{reinterpret_cast<const uint32_t*>(hits), inst_ids, g.inst_tris, accel->instance_count, 0};
+    if (p.want_vertices) RT_HIP(rta::sort_reserve(ctx->sortbuf, g.buckets, n, s));
+    if (p.want_frames) RT_HIP(rta::sort_reserve(ctx->sortbuf2, accel->instance_count, n, s));
+    RT_HIP(rta::bucket_rays(keys, n, s, p.want_vertices ? &ctx->sortbuf : nullptr, g.buckets, g.shift, &p.vb,
+                            p.want_frames ? &ctx->sortbuf2 : nullptr, accel->instance_count, &p.fb));
     RT_HIP(rtk_launch_backward_inst_tiles(p, s));
     if (p.want_vertices) RT_HIP(rta::gather_vertices(g, ctx->sortbuf, n, d_vertices, s));
     if (p.want_frames)
