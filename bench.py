@@ -58,7 +58,7 @@ def measured_traffic(info, variant):
     known size), or None when the kernel source or configuration differs."""
     if not os.path.exists(TRAFFIC_FILE):
         return None
-    name = "trace_kernel<%d, %d, %d, false, false, 0, false>" % (
+    name = "trace_kernel<%d, %d, %d, false, false, 0, true, false>" % (
         info["node_width"], variant[0], variant[1])
     sha, val = None, None
     with open(TRAFFIC_FILE) as f:
@@ -76,7 +76,7 @@ def measured_valu(info, variant):
     the kernel source or configuration differs."""
     if not os.path.exists(SQ_FILE):
         return None
-    name = "trace_kernel<%d, %d, %d, false, false, 0, false>" % (
+    name = "trace_kernel<%d, %d, %d, false, false, 0, true, false>" % (
         info["node_width"], variant[0], variant[1])
     sha, kern, ctr = None, None, {}
     with open(SQ_FILE) as f:
@@ -350,8 +350,9 @@ def main():
                      "frac_with_finalize": round(achieved_with_finalize / HBM_PEAK_GBS, 4),
                      "traffic_frac": None if traffic is None else round(
                          traffic / (mean_kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                     "limiter": "VALU issue (see valu): the measured HBM traffic is below the "
-                                "algorithmic bytes, most fetches hit the caches",
+                     "limiter": "L1 accesses (a divergent 16-byte load takes a CU one cycle per lane): "
+                                "the measured HBM traffic is below the algorithmic bytes, most "
+                                "fetches hit the caches",
                      "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4),
                      "valu": None if valu is None else {
                          "bound": "alu", "wave_instructions": valu[0],
@@ -601,8 +602,7 @@ def batched_bench(args, torch, np, api, _capi, workloads, ctx, stream):
     ms_b, _ = timed(batched, steps, stream, torch)
     # fixed costs of one rt_trace_closest call: the host time to enqueue it
     # (Python ctypes call included; the first 64 meshes' calls, so the
-    # queue never fills) and the device time of a 64-ray launch (fill,
-    # persistent traversal and overflow-finalize kernels back to back)
+    # queue never fills) and the device time of a 64-ray launch
     torch.cuda.synchronize()
     t_host = time.perf_counter()
     for a, r, h in list(zip(accs, rays, hits))[:64]:

@@ -2,15 +2,14 @@
 //
 // One ray per lane (the paper's §3.3 observes that rays through pixels are
 // independent and map to parallel threads).  Waves are persistent: lanes
-// whose ray is finished take new rays from a global counter, one atomic per
-// wave, with lane offsets from a ballot and a prefix popcount (wave-level
-// compaction).  Each lane walks a W-wide BVH (§6.2) with a stack (the
-// traversal paragraph of §6.2) whose top S entries live in LDS and whose
-// deeper entries spill to a global buffer (§7.5 describes the shared-memory
-// stack with a global fallback).  Internal nodes are visited until every
-// live lane of the wave has reached a leaf, then the leaves are tested
-// (Aila & Laine 2009, "while-while").  No matrix cores: this is pointer
-// chasing, not a dense contraction.
+// whose ray is finished take new rays from the wave's share, which is renewed
+// in chunks from one queue per die, with lane offsets from a ballot and a
+// prefix popcount (wave-level compaction).  Each lane walks a W-wide BVH
+// (§6.2) with a stack (the traversal paragraph of §6.2) whose first entries
+// live in LDS and whose deeper entries spill to a global buffer (§7.5
+// describes the shared-memory stack with a global fallback).  A wave takes
+// node visits and triangle tests step by step, whichever serves more of its
+// lanes.  No matrix cores: this is pointer chasing, not a dense contraction.
 //
 // Numerics: float32 traversal with a conservative slab test (boxes are exact
 // float32 bounds; the far distance is widened by 2*gamma(3), Ize 2013) and a
@@ -519,7 +518,7 @@ __device__ __forceinline__ void finalize_index(const TraceParams& P, uint32_t i)
 // a second one or a frame change, so it can serve either step.  Running each
 // phase until no lane of the wave had work left in it, as before, left 36% of
 // the lanes busy in node visits and 29% in triangle tests on incoherent rays;
-// choosing step by step leaves about 64% and 31%.
+// choosing step by step leaves about 65% and 33%.
 template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool OFF32, bool COUNT = false>
 __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   constexpr bool CULL = !ANY && MODE != 3;
