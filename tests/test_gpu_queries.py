@@ -91,6 +91,28 @@ def test_all_hits_dense_soup(gpu, orc, width):
     acc.close()
 
 
+@pytest.mark.parametrize("cap", [1, 2, 3, 4, 5, 7, 9, 16, 17])
+def test_list_lengths(gpu, cap):
+    """Hits are inserted four entries at a time: lists shorter, as long as and
+    longer than that are the heads of the longest ones bit for bit (rays
+    through many layers, their hits in no order)."""
+    torch, api, ctx = gpu
+    rng = wl.rng_for(221)
+    V, I = wl.random_triangle_soup(rng, 2001, 0.2)
+    rays = wl.box_rays(rng, 1023, 0.0, 1.0)
+    acc = to_gpu_scene(api, torch, ctx, wl.Scene([wl.Mesh(V, I)]))
+    h, ii, c = _all(gpu, acc, rays, 64)  # the largest capacity
+    assert c.max() > cap
+    got = _all(gpu, acc, rays, cap)
+    for a, b in zip(got, (h[:, :cap], ii[:, :cap], c)):
+        assert np.array_equal(np.ascontiguousarray(a).view(np.uint32), np.ascontiguousarray(b).view(np.uint32))
+    tri = h[:, :, 1].copy().view(np.uint32)
+    for r in np.flatnonzero(c)[:64]:
+        k = min(int(c[r]), 64)
+        assert len(set(tri[r, :k].tolist())) == k and (np.diff(h[r, :k, 0]) >= -1e-5).all()
+    acc.close()
+
+
 def test_all_hits_instances(gpu, orc):
     torch, api, ctx = gpu
     W = wl.aimed_instances(n_inst=8, n_rays=8192, k=221)
