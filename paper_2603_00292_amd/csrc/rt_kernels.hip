@@ -830,8 +830,7 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
           const uint32_t rec = leaf & RT_LEAF_FIRST_MASK;
           const float4* tp = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(g.tris) + (size_t)(rec * 48u));
           const float4 A = tp[0], B = tp[1], C = tp[2];
-          leaf += 1u - (1u << RT_LEAF_COUNT_SHIFT);
-          if (leaf < (1u << RT_LEAF_COUNT_SHIFT)) leaf = 0;
+          leaf = rt_leaf_rest(leaf);
           float t;
           if (tri_test(A, B, C, r, t) && t >= r.tmin && t <= best_t) {
             const uint32_t prim = __float_as_uint(A.w);

@@ -47,6 +47,14 @@ static inline uint32_t rt_make_leaf(uint32_t first, uint32_t count) {
 }
 static inline uint32_t rt_make_inst(uint32_t inst) { return RT_LEAF_BIT | RT_INST_BIT | inst; }
 
+// The rest of a leaf (count << RT_LEAF_COUNT_SHIFT | first, count >= 1) after
+// its first triangle, 0 when there is none.  The count is looked at before the
+// step: the record after RT_LEAF_FIRST_MASK would carry into it, and a leaf may
+// end with that record (RT_MAX_TRI_RECORDS).
+constexpr uint32_t rt_leaf_rest(uint32_t leaf) {
+  return leaf < (2u << RT_LEAF_COUNT_SHIFT) ? 0u : leaf + 1u - (1u << RT_LEAF_COUNT_SHIFT);
+}
+
 struct rt_tri_rec {
   float p0x, p0y, p0z;
   uint32_t prim;
