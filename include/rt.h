@@ -509,7 +509,12 @@ rt_status rt_batch_plan_create(rt_context ctx, const rt_accel* accels, const rt_
 rt_status rt_batch_plan_create_instances(rt_context ctx, const rt_accel* accels, const rt_ray* const* rays,
                                          rt_hit* const* hits, uint32_t* const* inst_ids, const uint32_t* counts,
                                          uint32_t batch_count, rt_batch_plan* out);
-/* Enqueues the whole batch: a queue reset and one persistent kernel launch. */
+/* Enqueues the whole batch: one persistent traversal launch (after a queue
+ * reset when the rays are more than the chip takes at once) and the float64
+ * finalize.  The launches of a plan share its scratch: one on another stream
+ * than the last waits for it.  Replays of the plan's graph, and launches that
+ * the caller captures, are not ordered by the library: they must not overlap
+ * one another or a launch of the same plan. */
 rt_status rt_batch_plan_launch(rt_batch_plan plan, void* stream);
 /* Captures the launch into a HIP graph (queue reset by a fill kernel, not a
  * memset node) and instantiates it; *out is a hipGraphExec_t owned by the

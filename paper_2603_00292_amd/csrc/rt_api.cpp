@@ -90,7 +90,7 @@ struct LaunchShape {
 
 // device scratch of one launch: queue counter + global spill stack
 struct Scratch {
-  uint32_t* counter = nullptr;   // ray queue heads (kRtCounterWords, zero between launches)
+  uint32_t* counter = nullptr;   // ray queue heads (kRtCounterWords)
   uint32_t* gstack = nullptr;
   size_t gstack_words = 0;
 };
@@ -184,6 +184,9 @@ struct rt_batch_plan_s {
   const void* kernel = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
+  hipEvent_t last_event = nullptr;           // after the last launch (ordered across streams)
+  hipStream_t last_stream = nullptr;
+  bool has_last = false;
 };
 
 namespace {
@@ -221,19 +224,9 @@ uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
   return std::min((uint32_t)per_cu, (uint32_t)kRtWavesPerCu * 64u / (uint32_t)wg) * (uint32_t)std::max(cu_count, 1);
 }
 
-// Makes sure scratch holds zeroed counters and a spill stack of `words` words.
+// Makes sure scratch holds the counters and a spill stack of `words` words.
 rt_status ensure_scratch(Scratch& s, size_t words) {
-  if (!s.counter) {
-    uint32_t* c = nullptr;
-    RT_HIP(rt_malloc(&c, kRtCounterWords * sizeof(uint32_t)));
-    hipError_t e = hipMemset(c, 0, kRtCounterWords * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-      (void)hipFree(c);
-      return fail(RT_ERROR_HIP, "zeroing the queue counters: %s", hipGetErrorString(e));
-    }
-    s.counter = c;
-  }
+  if (!s.counter) RT_HIP(rt_malloc(&s.counter, kRtCounterWords * sizeof(uint32_t)));
   if (words > s.gstack_words) {
     if (s.gstack) {
       RT_HIP(hipDeviceSynchronize());
@@ -1306,6 +1299,7 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   }
   p.counts = counts;
   p.cap = cap;
+  if (shape.chunk != 0u) RT_HIP(rtk_launch_queue_reset(counter, s));
   size_t tslot = ctx->tbeg.empty() ? 0 : (size_t)(ctx->trecorded % ctx->tbeg.size());
   if (!ctx->tbeg.empty()) RT_HIP(hipEventRecord(ctx->tbeg[tslot], s));
   RT_HIP(rtk_launch_trace(kern, blocks, wg, p, s));
@@ -2011,9 +2005,14 @@ static rt_status plan_create(rt_context ctx, const rt_accel* accels, const rt_ra
     free_scratch(p->scratch);
     if (p->descs) (void)hipFree(p->descs);
     if (p->offsets) (void)hipFree(p->offsets);
+    if (p->last_event) (void)hipEventDestroy(p->last_event);
     delete p;
     return e;
   };
+  if (hipEventCreateWithFlags(&p->last_event, hipEventDisableTiming) != hipSuccess) {
+    p->last_event = nullptr;
+    return bail(fail(RT_ERROR_HIP, "rt_batch_plan_create: hipEventCreate failed"));
+  }
   std::vector<BatchDesc> d(batch_count);
   std::vector<uint32_t> off(batch_count + 1, 0);
   for (uint32_t b = 0; b < batch_count; ++b) {
@@ -2078,6 +2077,7 @@ static rt_status enqueue_plan(rt_batch_plan p, hipStream_t s) {
   q.refill_min = p->ctx->refill_min;
   q.status = p->ctx->status;
   q.root = RT_CHILD_EMPTY;
+  if (p->shape.chunk != 0u) RT_HIP(rtk_launch_queue_reset(p->scratch.counter, s));
   RT_HIP(rtk_launch_trace(p->kernel, p->shape.blocks, p->workgroup, q, s));
   RT_HIP(rtk_launch_finalize(p->two_level, 1, q, s));
   return RT_SUCCESS;
@@ -2088,13 +2088,23 @@ rt_status rt_batch_plan_launch(rt_batch_plan plan, void* stream) {
   if (plan->total == 0) return ok();
   rt_status st = check_device(plan->ctx->device);
   if (st != RT_SUCCESS) return st;
-  {
-    std::lock_guard<std::mutex> lk(plan->ctx->mu);
-    st = take_overflow(plan->ctx, "rt_batch_plan_launch");
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  std::lock_guard<std::mutex> lk(plan->ctx->mu);
+  st = take_overflow(plan->ctx, "rt_batch_plan_launch");
+  if (st != RT_SUCCESS) return st;
+  // the plan's launches share its scratch: on another stream than the last
+  // one, this launch waits for it (a capture orders only what it holds)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  const bool ordered = capture == hipStreamCaptureStatusNone;
+  if (ordered && plan->has_last && plan->last_stream != s) RT_HIP(hipStreamWaitEvent(s, plan->last_event, 0));
+  st = enqueue_plan(plan, s);
+  if (st != RT_SUCCESS) return st;
+  if (ordered) {
+    RT_HIP(hipEventRecord(plan->last_event, s));
+    plan->last_stream = s;
+    plan->has_last = true;
   }
-  if (st != RT_SUCCESS) return st;
-  st = enqueue_plan(plan, static_cast<hipStream_t>(stream));
-  if (st != RT_SUCCESS) return st;
   return ok();
 }
 
@@ -2137,6 +2147,7 @@ rt_status rt_batch_plan_destroy(rt_batch_plan plan) {
   free_scratch(plan->scratch);
   if (plan->descs) (void)hipFree(plan->descs);
   if (plan->offsets) (void)hipFree(plan->offsets);
+  (void)hipEventDestroy(plan->last_event);
   delete plan;
   return ok();
 }

@@ -37,9 +37,7 @@ struct TraceParams {
   // touched.  Otherwise tiles of 1 << tile_shift rays are dealt to kRtQueues
   // queues in turn; the shares of the waves of workgroups q, q + kRtQueues,
   // ... open queue q, and counter[q * kRtQueueStride] counts the rays of its
-  // chunks given out.  The word after the last queue's counts the workgroups
-  // that are done; the last one zeroes all of them, so they are zero between
-  // launches.
+  // chunks given out (rtk_launch_queue_reset zeroes them before the launch).
   uint32_t* counter;
   uint32_t share, chunk, tile_shift;
   uint32_t* gstack;      // global stack: per thread of the grid, the entries past the LDS ones
@@ -74,7 +72,7 @@ constexpr uint32_t kRtRangesPerWave = 64;
 // Ray queues of a launch (one per die of the chip) and the words between
 // their heads (a cache line each).
 constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
-constexpr uint32_t kRtCounterWords = (kRtQueues + 1) * kRtQueueStride;
+constexpr uint32_t kRtCounterWords = kRtQueues * kRtQueueStride;
 
 // waves that run at once on a CU at most (see resident_blocks)
 constexpr int kRtWavesPerCu = 20;
@@ -168,6 +166,10 @@ struct AoParams {
 // always use 64-bit addresses.
 const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode, bool wide);
 const void* rtk_count_kernel(int width, bool any, bool inst);
+// Zeroes the queue heads of the next trace launch with chunks on `stream` (a
+// kernel: it may be captured).  Every such launch is preceded by it, so
+// whatever an earlier one left there has no effect.
+hipError_t rtk_launch_queue_reset(uint32_t* counter, hipStream_t stream);
 hipError_t rtk_launch_trace(const void* kern, uint32_t grid, uint32_t wg, const TraceParams& p,
                             hipStream_t stream);
 // float64 finalize of closest hits written by a trace launch with the same params

@@ -549,7 +549,7 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   // share of LDS
   constexpr int kTop = OFF32 && W >= 4 ? rtk_top_nodes(W, WG, Stk::kLdsEnd + (INST ? 24 * WG : 0)) : 0;
   __shared__ float4 lds_top[kTop > 0 ? kTop * kNodeParts<W> : 1];
-  __shared__ uint32_t lds_done, lds_empty;   // waves done; queues found used up (bit mask)
+  __shared__ uint32_t lds_empty;   // queues found used up (bit mask)
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
   const uint32_t gtid = blockIdx.x * WG + tid;
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   st.gstride = P.gstride;
   st.cap = P.max_stack;
   st.init(tid);
-  if (tid == 0) lds_done = lds_empty = 0;
+  if (tid == 0) lds_empty = 0;
   const uint32_t n_top = min((uint32_t)kTop, P.top_nodes);
   if constexpr (kTop > 0) {
     const float4* src = reinterpret_cast<const float4*>(P.nodes);
@@ -896,16 +896,6 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
             cur = I.root;
           }
         }
-      }
-    }
-  }
-  if (P.chunk != 0u && lane == 0) {
-    // the last wave of the launch to leave the queues zeroes them for the
-    // next launch
-    if (atomicAdd(&lds_done, 1u) == kWaves - 1u) {
-      if (atomicAdd(P.counter + kRtQueues * kRtQueueStride, 1u) == gridDim.x - 1u) {
-        for (uint32_t v = 0; v <= kRtQueues; ++v)
-          __hip_atomic_store(P.counter + v * kRtQueueStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
@@ -1647,6 +1637,10 @@ __global__ __launch_bounds__(256) void ao_resolve_kernel(const uint8_t* occ, uin
   ao[i] = (float)c / (float)samples;
 }
 
+__global__ void queue_reset_kernel(uint32_t* counter) {
+  if (threadIdx.x < kRtQueues) counter[threadIdx.x * kRtQueueStride] = 0u;
+}
+
 }  // namespace rtk
 
 // ---------------------------------------------------------------------------
@@ -1737,6 +1731,11 @@ const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, 
     case 8: return pick_s<8>(stack, wg, any, inst, mode, wide);
     default: return nullptr;
   }
+}
+
+hipError_t rtk_launch_queue_reset(uint32_t* counter, hipStream_t stream) {
+  void* args[] = {&counter};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&rtk::queue_reset_kernel), dim3(1), dim3(64), args, 0, stream);
 }
 
 hipError_t rtk_launch_trace(const void* kern, uint32_t grid, uint32_t wg, const TraceParams& p,
