@@ -171,9 +171,7 @@ typedef struct rt_accel_info {
  * allocated, and objects it was to create are not created.  Unset or 0:
  * no failure (this call disarms an earlier one). */
 rt_status rt_context_create(int hip_device, rt_context* out);
-/* Frees the context's scratch (global stacks, queue counters, the ray-range
- * lists of rt_trace_closest).  An accel
- * keeps the context it was built with and traces with that context's
+/* Frees the context's scratch (global stacks, queue heads).  An accel keeps the context it was built with and traces with that context's
  * variant and scratch, so destroy every accel and batch plan of a context
  * before the context.  Trace calls of one context on different streams are
  * ordered one after another (they share the scratch). */
@@ -241,17 +239,20 @@ rt_status rt_trace_closest(rt_accel accel, const rt_ray* rays, uint32_t n, rt_hi
 /* rt_trace_closest for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, same kernels and bit-identical results, but
- * the launch's scratch (ray-queue counters, the per-wave ray-range lists of
- * the float64 finalize and the global spill stack) lives in a fixed device
- * array of RT_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it
- * runs on until the process ends; the call allocates nothing.  The grid is
- * narrowed when the spill stack of a full grid would not fit.  Every call on
+ * the launch's scratch (ray-queue heads and the global spill stack) lives in
+ * a fixed device array of a little more than RT_NOALLOC_SCRATCH_BYTES that the
+ * library holds on every GPU it runs on until the process ends; the call
+ * allocates nothing.  The grid is narrowed when the spill stack of a full
+ * grid would not fit.  Every call on
  * a GPU shares that GPU's array: calls that overlap on one GPU (from
  * different contexts, or on streams the caller does not order) race and
  * must not be issued; calls of one context are ordered as usual.
- * Errors: as rt_trace_closest, and RT_ERROR_INVALID_VALUE when n rays need
- * more scratch than the array holds (about 2^28 rays at the default refill
- * setting). */
+ * Errors: as rt_trace_closest, and RT_ERROR_INVALID_VALUE when
+ * 64 + 2 (n / r + 1) + 4 w + w max(b - e, 1) 32-bit words, with r idle lanes
+ * to a refill (32 by default), workgroups of w threads, e stack entries of the
+ * variant and the accel's stack bound b, exceed RT_NOALLOC_SCRATCH_BYTES
+ * (about 2^28 rays at the defaults).  This is a limit on the calls, not what
+ * one of them uses. */
 #define RT_NOALLOC_SCRATCH_BYTES (64u << 20)
 rt_status rt_trace_closest_noalloc(rt_accel accel, const rt_ray* rays, uint32_t n, rt_hit* hits,
                                    uint32_t* inst_ids, void* stream);

@@ -286,13 +286,14 @@ rt_status check_device(int dev) {
 // GPU's copy only through the address hipGetSymbolAddress returns with that
 // GPU current (noalloc_setup), never through the array's name.
 constexpr size_t kNoAllocWords = RT_NOALLOC_SCRATCH_BYTES / sizeof(uint32_t);
+constexpr size_t kNoAllocArray = rtk_noalloc_array(kNoAllocWords);
 constexpr int kNoAllocMaxDevices = 64;
 std::mutex g_noalloc_mu;
 uint32_t* g_noalloc_ptr[kNoAllocMaxDevices] = {};
 
 }  // namespace
 
-static __device__ __align__(256) uint32_t scratch[kNoAllocWords];
+static __device__ __align__(256) uint32_t scratch[kNoAllocArray];
 
 namespace {
 
@@ -316,14 +317,6 @@ uint32_t* noalloc_ptr(int dev) {
   if (dev < 0 || dev >= kNoAllocMaxDevices) return nullptr;
   std::lock_guard<std::mutex> lk(g_noalloc_mu);
   return g_noalloc_ptr[dev];
-}
-
-// Whether rt_trace_closest_noalloc takes a launch: the array is budgeted for
-// the counters, 256 words per wave and the spill stack of one workgroup, and
-// two words per refill_min rays.
-bool noalloc_accepts(uint32_t n, uint32_t refill_min, const rt_variant& v, uint32_t max_stack) {
-  const size_t spill = max_stack > v.stack_entries ? max_stack - v.stack_entries : 1;
-  return 64 + 2 * ((size_t)n / refill_min + 1) + (v.workgroup / 64u) * 256u + spill * v.workgroup <= kNoAllocWords;
 }
 
 // Reports (and clears) a stack overflow flagged by an earlier traversal on
@@ -1251,11 +1244,11 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
     // narrowed until it fits
     uint32_t* base = noalloc_ptr(a->device);
     if (!base) return fail(RT_ERROR_HIP, "rt_trace_closest_noalloc: no scratch on device %d", a->device);
-    if (!noalloc_accepts(n, ctx->refill_min, v, a->max_stack) || spill * wg > kNoAllocWords - kRtCounterWords)
+    if (rtk_noalloc_budget(n, ctx->refill_min, v.stack_entries, wg, a->max_stack) > kNoAllocWords)
       return fail(RT_ERROR_INVALID_VALUE,
-                  "rt_trace_closest_noalloc: %u rays with a stack bound of %u need more than the %u-byte "
+                  "rt_trace_closest_noalloc: %u rays with a stack bound of %u exceed the limit of the %u-byte "
                   "scratch", n, a->max_stack, (unsigned)RT_NOALLOC_SCRATCH_BYTES);
-    const uint32_t fit = (uint32_t)std::min<size_t>(resident, (kNoAllocWords - kRtCounterWords) / (spill * wg));
+    const uint32_t fit = (uint32_t)std::min<size_t>(resident, (kNoAllocArray - kRtCounterWords) / (spill * wg));
     if (shape.blocks > fit) shape = launch_shape(n, wg, fit);
     counter = base;
     gstack = base + kRtCounterWords;

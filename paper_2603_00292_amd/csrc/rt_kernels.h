@@ -6,6 +6,7 @@
 
 #include "../../include/rt.h"
 #include "accumulate.h"
+#include "rt_launch.h"
 #include "rt_layout.h"
 
 // One batch entry of a batched plan (device copy).
@@ -69,31 +70,15 @@ struct TraceParams {
 // takes no more, so the chunks are sized for a quarter of that (launch_shape).
 constexpr uint32_t kRtRangesPerWave = 64;
 
-// Ray queues of a launch (one per die of the chip) and the words between
-// their heads (a cache line each).
-constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
-constexpr uint32_t kRtCounterWords = kRtQueues * kRtQueueStride;
-
 // waves that run at once on a CU at most (see resident_blocks)
 constexpr int kRtWavesPerCu = 20;
 
-// LDS stack entries of a lane in the variant with `stack` entries: 4-byte
-// references for any-hit and all-hit queries; closest hits keep an 8-byte
-// (distance, reference) entry, and 5/8 as many, which holds eight workgroups
-// of 256 threads in a CU's 160 KB.
-constexpr int rtk_lds_entries(int stack, bool cull) { return cull ? stack * 5 / 8 : stack; }
 // Nodes of W-wide trees that fit the rest of a workgroup's LDS after `used`
 // bytes, when kRtWavesPerCu waves are to share a CU's 160 KB (which it gives
 // out in pieces of 1,280 bytes)
 constexpr int rtk_top_nodes(int width, int wg, int used) {
   const int budget = 160 * 1024 / (kRtWavesPerCu * 64 / wg) / 1280 * 1280 - 64;
   return budget > used ? (budget - used) / (28 * width) : 0;
-}
-constexpr bool rtk_stack_culls(bool any, int mode) { return !any && mode != 3; }
-// global stack words per thread (4-byte references) for a bound of max_stack entries
-inline size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode) {
-  const uint32_t lds = (uint32_t)rtk_lds_entries((int)stack, rtk_stack_culls(any, mode));
-  return max_stack > lds ? max_stack - lds : 1u;
 }
 
 // Single-level adjoint (a workgroup of 1024 threads per tile of rta::kTile
