@@ -185,8 +185,8 @@ struct Pending {
 };
 
 // Writes wide node `p.wi` for binary node `p.bi`; its internal children are
-// numbered and appended to `next`.
-void expand(Collapse& C, const Pending& p, std::vector<Pending>& next) {
+// numbered and written to `next` (at most 8).  Returns how many there are.
+int expand(Collapse& C, const Pending& p, Pending* next) {
   const uint32_t bi = p.bi, wi = p.wi, depth = p.depth, stack_above = p.stack_above;
   const std::vector<BNode>& N = C.B->nodes;
   const int W = C.W;
@@ -246,14 +246,16 @@ void expand(Collapse& C, const Pending& p, std::vector<Pending>& next) {
     uint32_t zero = 0;
     std::memcpy(&nd[7 * W + i], &zero, 4);
   }
+  int count = 0;
   for (size_t i = 0; i < kids.size(); ++i)
-    if (child_node[i] != RT_CHILD_EMPTY) next.push_back(Pending{kids[i], child_node[i], depth + 1, stack_here});
+    if (child_node[i] != RT_CHILD_EMPTY) next[count++] = Pending{kids[i], child_node[i], depth + 1, stack_here};
+  return count;
 }
 
 void collapse(Collapse& C, const Pending& p) {
-  std::vector<Pending> next;
-  expand(C, p, next);
-  for (const Pending& q : next) collapse(C, q);
+  Pending next[8];
+  const int count = expand(C, p, next);
+  for (int i = 0; i < count; ++i) collapse(C, next[i]);
 }
 
 // The upper levels are numbered breadth first (the traversal keeps the first
@@ -265,8 +267,9 @@ void collapse_tree(Collapse& C) {
     std::vector<Pending> next;
     const bool breadth = C.out->node_count < kBreadthFirstNodes;
     for (const Pending& p : level) {
-      if (breadth) expand(C, p, next);
-      else collapse(C, p);
+      Pending kids[8];
+      if (!breadth) collapse(C, p);
+      else next.insert(next.end(), kids, kids + expand(C, p, kids));
     }
     level.swap(next);
   }
