@@ -83,11 +83,6 @@ bool valid_variant(const rt_variant& v) {
   return s_ok && wg_ok;
 }
 
-// Grid and ray shares of a traversal launch over n rays.
-struct LaunchShape {
-  uint32_t blocks, share, chunk, tile_shift;  // see TraceParams
-};
-
 // device scratch of one launch: queue counter + global spill stack
 struct Scratch {
   uint32_t* counter = nullptr;   // ray queue heads (kRtCounterWords)
@@ -238,38 +233,6 @@ rt_status ensure_scratch(Scratch& s, size_t words) {
     s.gstack_words = words;
   }
   return RT_SUCCESS;
-}
-
-// Up to 64 rays per resident wave, every wave takes its rays at once, in one
-// share, and the queues are not used.  Few rays are spread over the chip's
-// 1,024 SIMDs first (64 rays on a 20,480-triangle mesh: 26 us a call with one
-// ray a wave, 35 with 32), then 32 to a wave (65,536 rays: 49 us; 16 to a
-// wave 58).  Beyond, waves take a chunk each and then more from the queues: 64
-// rays, or more when the average wave would need more than a quarter of its
-// kRtRangesPerWave ranges (the waves together can then hold four times the
-// rays, so a wave with a full list always leaves the rest to others).  A queue
-// gets at least 16 tiles, of at most 32,768 rays (tiles of 256 to 65,536 rays
-// are within 3% of each other).
-LaunchShape launch_shape(uint32_t n, uint32_t wg, uint32_t max_blocks) {
-  LaunchShape s;
-  const uint32_t wpb = wg / 64u;
-  const uint64_t waves_max = (uint64_t)max_blocks * wpb;
-  s.tile_shift = 0;
-  if (n <= waves_max * 64u) {
-    const uint32_t spread = std::min(32u, (n + 1023u) / 1024u);
-    s.share = std::max(std::max(1u, spread), (uint32_t)((n + waves_max - 1) / waves_max));
-    s.blocks = std::max(1u, (n + s.share * wpb - 1) / (s.share * wpb));
-    s.chunk = 0;
-  } else {
-    s.blocks = max_blocks;
-    s.chunk = 64;
-    while ((uint64_t)s.chunk * (kRtRangesPerWave / 4u) * waves_max < n) s.chunk *= 2;
-    s.share = s.chunk;
-    while ((1u << s.tile_shift) < s.chunk ||
-           (s.tile_shift < 15u && ((uint64_t)kRtQueues * 16u << (s.tile_shift + 1)) <= n))
-      ++s.tile_shift;
-  }
-  return s;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

@@ -33,11 +33,7 @@ struct TraceParams {
   rt_hit* hits;
   uint32_t* inst_ids;
   uint8_t* occluded;
-  // Rays are given out in fixed shares of `share` per wave, and beyond those in
-  // chunks.  chunk == 0: the shares cover all rays, the counters are not
-  // touched.  Otherwise tiles of 1 << tile_shift rays are dealt to kRtQueues
-  // queues in turn; the shares of the waves of workgroups q, q + kRtQueues,
-  // ... open queue q, and counter[q * kRtQueueStride] counts the rays of its
+  // See LaunchShape; counter[v * kRtQueueStride] counts the rays of queue v's
   // chunks given out (rtk_launch_queue_reset zeroes them before the launch).
   uint32_t* counter;
   uint32_t share, chunk, tile_shift;
@@ -63,12 +59,6 @@ struct TraceParams {
   uint32_t* counts;      // mode 3: hits per ray
   uint32_t cap;          // mode 3: list entries per ray
 };
-
-// Closest queries on one accel (mode 0) finalize their hits inside the
-// traversal kernel, each wave the ray ranges it took once they are all
-// finished; a wave remembers at most this many ranges (one per lane) and then
-// takes no more, so the chunks are sized for a quarter of that (launch_shape).
-constexpr uint32_t kRtRangesPerWave = 64;
 
 // waves that run at once on a CU at most (see resident_blocks)
 constexpr int kRtWavesPerCu = 20;

@@ -605,20 +605,10 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   // sizes the chunks so that this leaves rays to others).
   constexpr uint32_t kWaves = WG / 64u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t die = blockIdx.x % kRtQueues, slot = blockIdx.x / kRtQueues;
-  // place of position p of queue v in the ray order; rays of queue v taken by
-  // the fixed shares
-  auto ray_at = [&](uint32_t v, uint32_t p) {
-    return ((((p >> P.tile_shift) * kRtQueues) + v) << P.tile_shift) + (p & ((1u << P.tile_shift) - 1u));
-  };
-  auto shared_out = [&](uint32_t v) { return (gridDim.x + kRtQueues - 1u - v) / kRtQueues * kWaves * P.share; };
-  uint32_t q_next, queue = die;
-  if (P.chunk == 0u) {
-    const uint32_t per = gridDim.x / kRtQueues, rem = gridDim.x % kRtQueues;
-    q_next = ((die * per + min(die, rem) + slot) * kWaves + wave) * P.share;
-  } else {
-    q_next = ray_at(die, (slot * kWaves + wave) * P.share);
-  }
+  auto ray_at = [&](uint32_t v, uint32_t p) { return rt_ray_at(P.tile_shift, v, p); };
+  auto shared_out = [&](uint32_t v) { return rt_shared_out(gridDim.x, kWaves, P.share, v); };
+  uint32_t q_next = rt_first_ray(blockIdx.x, wave, gridDim.x, kWaves, P.share, P.chunk, P.tile_shift);
+  uint32_t queue = blockIdx.x % kRtQueues;   // the die's
   q_next = min(P.n, q_next);
   uint32_t q_end = min(P.n, q_next + P.share);
   bool drained = P.chunk == 0u;

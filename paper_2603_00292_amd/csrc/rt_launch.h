@@ -1,13 +1,81 @@
-// rt_launch.h -- scratch of a traversal launch (librtq internal; host and
-// device, no HIP).
+// rt_launch.h -- grid, ray shares and scratch of a traversal launch (librtq
+// internal; host and device, no HIP).
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 // Ray queues of a launch (one per die of the chip) and the words between
 // their heads (a cache line each).
 constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
 constexpr uint32_t kRtCounterWords = kRtQueues * kRtQueueStride;
+
+// Closest queries on one accel (mode 0) finalize their hits inside the
+// traversal kernel, each wave the ray ranges it took once they are all
+// finished; a wave remembers at most this many ranges (one per lane) and then
+// takes no more, so the chunks are sized for a quarter of that (launch_shape).
+constexpr uint32_t kRtRangesPerWave = 64;
+
+// Grid and ray shares of a launch.  chunk == 0: wave w of workgroup b takes
+// `share` rays from rt_first_ray() on, and that is all of them.  Otherwise the
+// rays are dealt in tiles of 1 << tile_shift to the queues in turn; the waves
+// of workgroups q, q + kRtQueues, ... take the first shares of queue q (as long
+// as a chunk), and from there on all waves take chunks of whichever queue.
+struct LaunchShape {
+  uint32_t blocks, share, chunk, tile_shift;
+};
+
+// Up to 64 rays per resident wave, every wave takes its rays at once, in one
+// share, and the queues are not used.  Few rays are spread over the chip's
+// 1,024 SIMDs first (64 rays on a 20,480-triangle mesh: 26 us a call with one
+// ray a wave, 35 with 32), then 32 to a wave (65,536 rays: 49 us; 16 to a
+// wave 58).  Beyond, waves take a chunk each and then more from the queues: 64
+// rays, or more when the average wave would need more than a quarter of its
+// kRtRangesPerWave ranges (the waves together can then hold four times the
+// rays, so a wave with a full list always leaves the rest to others).  A queue
+// gets at least 16 tiles, of at most 32,768 rays (tiles of 256 to 65,536 rays
+// are within 3% of each other).
+inline LaunchShape launch_shape(uint32_t n, uint32_t wg, uint32_t max_blocks) {
+  LaunchShape s;
+  const uint32_t wpb = wg / 64u;
+  const uint64_t waves_max = (uint64_t)max_blocks * wpb;
+  s.tile_shift = 0;
+  if (n <= waves_max * 64u) {
+    const uint32_t spread = std::min(32u, (n + 1023u) / 1024u);
+    s.share = std::max(std::max(1u, spread), (uint32_t)((n + waves_max - 1) / waves_max));
+    s.blocks = std::max(1u, (n + s.share * wpb - 1) / (s.share * wpb));
+    s.chunk = 0;
+  } else {
+    s.blocks = max_blocks;
+    s.chunk = 64;
+    while ((uint64_t)s.chunk * (kRtRangesPerWave / 4u) * waves_max < n) s.chunk *= 2;
+    s.share = s.chunk;
+    while ((1u << s.tile_shift) < s.chunk ||
+           (s.tile_shift < 15u && ((uint64_t)kRtQueues * 16u << (s.tile_shift + 1)) <= n))
+      ++s.tile_shift;
+  }
+  return s;
+}
+
+// Place in the ray order of position p of queue v.  A queue's head runs past
+// its rays by at most a chunk for each wave of the launch, and fewer than 2^31
+// rays keep that below 2^32.
+constexpr uint32_t rt_ray_at(uint32_t tile_shift, uint32_t v, uint32_t p) {
+  return ((((p >> tile_shift) * kRtQueues) + v) << tile_shift) + (p & ((1u << tile_shift) - 1u));
+}
+// Rays of queue v that the first shares of `blocks` workgroups take.
+constexpr uint32_t rt_shared_out(uint32_t blocks, uint32_t waves, uint32_t share, uint32_t v) {
+  return (blocks + kRtQueues - 1u - v) / kRtQueues * waves * share;
+}
+// First ray of the share of wave `wave` of workgroup `block` (`waves` each).
+constexpr uint32_t rt_first_ray(uint32_t block, uint32_t wave, uint32_t blocks, uint32_t waves, uint32_t share,
+                                uint32_t chunk, uint32_t tile_shift) {
+  const uint32_t v = block % kRtQueues, slot = block / kRtQueues;
+  const uint32_t per = blocks / kRtQueues, rem = blocks % kRtQueues;
+  return chunk == 0u ? ((v * per + (v < rem ? v : rem) + slot) * waves + wave) * share
+                     : rt_ray_at(tile_shift, v, (slot * waves + wave) * share);
+}
 
 // LDS stack entries of a lane in the variant with `stack` entries: 4-byte
 // references for any-hit and all-hit queries; closest hits keep an 8-byte
