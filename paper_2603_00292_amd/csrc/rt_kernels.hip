@@ -1257,6 +1257,7 @@ __global__ __launch_bounds__(1024) void backward_inst_tile_kernel(BackwardInstPa
     }
   }
   if (P.want_vertices) bucket_starts(P.vb, vpos);
+  __syncthreads();  // both groupings scan in the same words of LDS
   if (P.want_frames) bucket_starts(P.fb, fpos);
   __syncthreads();
   // The ray, its gradient and the triangle of the thread's next ray, on their
