@@ -216,6 +216,9 @@ uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, wg, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 1;
+  hipFuncAttributes fa{};
+  if (hipFuncGetAttributes(&fa, kern) == hipSuccess)
+    per_cu = (int)std::min((uint32_t)per_cu, std::max(1u, rtk_lds_blocks((uint32_t)fa.sharedSizeBytes)));
   return std::min((uint32_t)per_cu, (uint32_t)kRtWavesPerCu * 64u / (uint32_t)wg) * (uint32_t)std::max(cu_count, 1);
 }
 

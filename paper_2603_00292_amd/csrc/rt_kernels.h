@@ -60,17 +60,6 @@ struct TraceParams {
   uint32_t cap;          // mode 3: list entries per ray
 };
 
-// waves that run at once on a CU at most (see resident_blocks)
-constexpr int kRtWavesPerCu = 20;
-
-// Nodes of W-wide trees that fit the rest of a workgroup's LDS after `used`
-// bytes, when kRtWavesPerCu waves are to share a CU's 160 KB (which it gives
-// out in pieces of 1,280 bytes)
-constexpr int rtk_top_nodes(int width, int wg, int used) {
-  const int budget = 160 * 1024 / (kRtWavesPerCu * 64 / wg) / 1280 * 1280 - 64;
-  return budget > used ? (budget - used) / (28 * width) : 0;
-}
-
 // Single-level adjoint (a workgroup of 1024 threads per tile of rta::kTile
 // rays): writes the ray gradients and places each hit ray's record in its
 // bucket for the vertex accumulation of accumulate.h.

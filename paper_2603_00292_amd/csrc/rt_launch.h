@@ -78,15 +78,37 @@ constexpr uint32_t rt_first_ray(uint32_t block, uint32_t wave, uint32_t blocks, 
 }
 
 // LDS stack entries of a lane in the variant with `stack` entries: 4-byte
-// references for any-hit and all-hit queries; closest hits keep an 8-byte
-// (distance, reference) entry, and 5/8 as many, which holds eight workgroups
-// of 256 threads in a CU's 160 KB.
-constexpr int rtk_lds_entries(int stack, bool cull) { return cull ? stack * 5 / 8 : stack; }
+// references for any-hit and all-hit queries; closest hits keep 8-byte
+// (distance, reference) entries, and as many as leave a CU's LDS to 20 waves:
+// 8, 10 and 13.  (With 5 of the 8, 2-wide nodes spilled more than the cull
+// saved: 400,003 incoherent rays 480 us against 437, workgroups of 64.)
+constexpr int rtk_lds_entries(int stack, bool cull) {
+  return !cull || stack <= 8 ? stack : stack <= 16 ? 10 : 13;
+}
 constexpr bool rtk_stack_culls(bool any, int mode) { return !any && mode != 3; }
 // global stack words per thread (4-byte references) for a bound of max_stack entries
 constexpr size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode) {
   const uint32_t lds = (uint32_t)rtk_lds_entries((int)stack, rtk_stack_culls(any, mode));
   return max_stack > lds ? max_stack - lds : 1u;
+}
+
+// A CU gives out its 160 KB of LDS in pieces of 1,280 bytes, which the runtime's
+// occupancy query does not count: it named 15 workgroups of 64 threads and
+// 10,756 bytes where 14 fit, and the last one then waited for a whole share of
+// another (250,007 incoherent rays 383 us against 331 before the shares).
+constexpr uint32_t kLdsBytes = 160 * 1024, kLdsPiece = 1280;
+constexpr uint32_t rtk_lds_blocks(uint32_t bytes) {
+  return bytes == 0u ? ~0u : kLdsBytes / ((bytes + kLdsPiece - 1u) / kLdsPiece * kLdsPiece);
+}
+
+// waves that run at once on a CU at most (see resident_blocks)
+constexpr int kRtWavesPerCu = 20;
+
+// Nodes of W-wide trees that fit the rest of a workgroup's LDS after `used`
+// bytes, when kRtWavesPerCu waves are to share a CU's
+constexpr int rtk_top_nodes(int width, int wg, int used) {
+  const int budget = (int)(kLdsBytes / (kRtWavesPerCu * 64 / wg) / kLdsPiece * kLdsPiece) - 64;
+  return budget > used ? (budget - used) / (28 * width) : 0;
 }
 
 // Scratch of rt_trace_closest_noalloc.  A launch is taken while the words
@@ -98,9 +120,9 @@ constexpr size_t rtk_noalloc_budget(uint32_t n, uint32_t refill_min, uint32_t st
   return 64 + 2 * ((size_t)n / refill_min + 1) + (wg / 64u) * 256u +
          (size_t)(max_stack > stack ? max_stack - stack : 1u) * wg;
 }
-// Words of the array behind it for a limit of `words`: closest hits keep 3/8
-// of the variant's entries fewer in LDS, 12 for 32 entries, so that the
-// deepest stack taken needs this much more (256 threads).
+// Words of the array behind it for a limit of `words`: closest hits keep fewer
+// than the variant's entries in LDS, 19 fewer of 32, so that the deepest stack
+// taken needs this much more (256 threads).
 constexpr size_t rtk_noalloc_array(size_t words) {
   return words + kRtCounterWords + (32u - (uint32_t)rtk_lds_entries(32, true)) * 256u;
 }

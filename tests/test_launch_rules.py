@@ -171,3 +171,48 @@ def test_every_ray_is_handed_out_once(tmp_path):
     that stop at their range limit, whatever the order in which the waves come;
     and no queue head wraps at the largest launches."""
     run_driver(tmp_path, RAYS)
+
+
+RESIDENT = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "rt_launch.h"
+int main() {
+  int failures = 0;
+  // what fits, piece by piece
+  for (uint32_t bytes = 1; bytes <= kLdsBytes; ++bytes) {
+    uint32_t pieces = 0, fit = 0;
+    while (pieces * kLdsPiece < bytes) ++pieces;
+    while ((fit + 1) * pieces * kLdsPiece <= kLdsBytes) ++fit;
+    if (rtk_lds_blocks(bytes) != fit) {
+      std::printf("%u bytes: %u, %u fit\n", bytes, rtk_lds_blocks(bytes), fit);
+      ++failures;
+    }
+  }
+  // the closest-hit stacks (and the sentinel entry) of every variant
+  for (uint32_t wg : {64u, 128u, 256u})
+    for (int stack : {8, 16, 32}) {
+      const uint32_t bytes = (uint32_t)(rtk_lds_entries(stack, true) + 1) * 8u * wg + 4u;
+      if (rtk_lds_blocks(bytes) * (wg / 64u) < (uint32_t)kRtWavesPerCu) {
+        std::printf("stack %d workgroup %u: %u waves\n", stack, wg, rtk_lds_blocks(bytes) * (wg / 64u));
+        ++failures;
+      }
+      // the upper levels fill what is left, and no more
+      for (int width : {4, 8}) {
+        const uint32_t full = bytes + (uint32_t)rtk_top_nodes(width, (int)wg, (int)bytes) * 28u * (uint32_t)width;
+        if (rtk_lds_blocks(full) * (wg / 64u) < (uint32_t)kRtWavesPerCu) {
+          std::printf("stack %d workgroup %u width %d: %u bytes\n", stack, wg, width, full);
+          ++failures;
+        }
+      }
+    }
+  std::printf("%d failures\n", failures);
+  return failures != 0;
+}
+"""
+
+
+def test_resident_waves(tmp_path):
+    """Workgroups that a CU's LDS holds, and the closest-hit stacks of all
+    variants at the number of waves that a launch is made for."""
+    run_driver(tmp_path, RESIDENT)
