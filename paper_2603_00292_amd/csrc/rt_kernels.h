@@ -34,7 +34,8 @@ struct TraceParams {
   uint32_t* inst_ids;
   uint8_t* occluded;
   // See LaunchShape; counter[v * kRtQueueStride] counts the rays of queue v's
-  // chunks given out (rtk_launch_queue_reset zeroes them before the launch).
+  // chunks given out, and carries kRtQueuesDone (rtk_launch_queue_reset zeroes
+  // the heads before the launch).
   uint32_t* counter;
   uint32_t share, chunk, tile_shift;
   uint32_t* gstack;      // global stack: per thread of the grid, the entries past the LDS ones
@@ -130,9 +131,8 @@ struct AoParams {
 // always use 64-bit addresses.
 const void* rtk_trace_kernel(int width, int stack, int wg, bool any, bool inst, int mode, bool wide);
 const void* rtk_count_kernel(int width, bool any, bool inst);
-// Zeroes the queue heads of the next trace launch with chunks on `stream` (a
-// kernel: it may be captured).  Every such launch is preceded by it, so
-// whatever an earlier one left there has no effect.
+// Zeroes the queue heads of a launch to come on `stream` (a kernel: it may be
+// captured).
 hipError_t rtk_launch_queue_reset(uint32_t* counter, hipStream_t stream);
 hipError_t rtk_launch_trace(const void* kern, uint32_t grid, uint32_t wg, const TraceParams& p,
                             hipStream_t stream);

@@ -630,7 +630,8 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
       queue = (queue + (uint32_t)__builtin_ctz(m)) % kRtQueues;
       uint32_t head = 0;
       if (lane == 0) head = atomicAdd(P.counter + queue * kRtQueueStride, P.chunk);
-      const uint32_t base = ray_at(queue, shared_out(queue) + __builtin_amdgcn_readfirstlane(head));
+      head = __builtin_amdgcn_readfirstlane(head);
+      const uint32_t base = ray_at(queue, shared_out(queue) + (head & ~kRtQueuesDone));
       if (base < P.n) {
         q_next = base;
         q_end = min(P.n, base + P.chunk);
@@ -640,13 +641,24 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
           drained = n_ranges == kRtRangesPerWave;
         }
       } else {
-        bool out = false;
-        if (lane < kRtQueues) {
-          const uint32_t h = __hip_atomic_load(P.counter + lane * kRtQueueStride, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-          out = ray_at(lane, shared_out(lane) + h) >= P.n;
+        // An address takes some 75 million accesses a second, and waves that
+        // all looked at all heads at the end of a launch waited for one another
+        // (327,681 rays on 1,310,720 triangles, one more than a share each: 247 us
+        // against 227 with the mark, workgroups of 64 314 against 235).  Of those
+        // that find no rays left, one in 32 marks the head that it came by, which
+        // tells the die's others.
+        uint32_t used = kAll;
+        if ((head & kRtQueuesDone) == 0u) {
+          bool out = false;
+          if (lane < kRtQueues) {
+            const uint32_t h = __hip_atomic_load(P.counter + lane * kRtQueueStride, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            out = ray_at(lane, shared_out(lane) + (h & ~kRtQueuesDone)) >= P.n;
+          }
+          used = (uint32_t)__ballot(out);
+          if (used == kAll && lane == 0 && (head & 31u * P.chunk) == 0u)
+            atomicOr(P.counter + queue * kRtQueueStride, kRtQueuesDone);
         }
-        const uint32_t used = (uint32_t)__ballot(out);
         if (lane == 0) atomicOr(&lds_empty, used);
       }
     }

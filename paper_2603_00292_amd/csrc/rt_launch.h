@@ -10,6 +10,8 @@
 // their heads (a cache line each).
 constexpr uint32_t kRtQueues = 8, kRtQueueStride = 32;
 constexpr uint32_t kRtCounterWords = kRtQueues * kRtQueueStride;
+// set in a head once no queue has rays left (the positions stay below it)
+constexpr uint32_t kRtQueuesDone = 0x80000000u;
 
 // Closest queries on one accel (mode 0) finalize their hits inside the
 // traversal kernel, each wave the ray ranges it took once they are all

@@ -135,7 +135,7 @@ static void heads(uint32_t n, uint32_t wg, uint32_t max_blocks) {
     end = std::max((end + s.chunk - 1) / s.chunk * s.chunk, shared);
     const uint64_t top = end + (uint64_t)waves * s.chunk;  // each wave adds a chunk once more than there is
     if (place(s.tile_shift, v, end) < n) bad("end of a queue", n, wg, max_blocks);
-    if (top >> 32 || place(s.tile_shift, v, top) >> 32 ||
+    if (top >= kRtQueuesDone || place(s.tile_shift, v, top) >> 32 ||
         place(s.tile_shift, v, top) != rt_ray_at(s.tile_shift, v, (uint32_t)top))
       bad("a head wraps", n, wg, max_blocks);
   }
