@@ -174,7 +174,9 @@ rt_status rt_context_create(int hip_device, rt_context* out);
 /* Frees the context's scratch (global stacks, queue heads).  An accel keeps the context it was built with and traces with that context's
  * variant and scratch, so destroy every accel and batch plan of a context
  * before the context.  Trace calls of one context on different streams are
- * ordered one after another (they share the scratch). */
+ * ordered one after another (they share the scratch); calls that the caller
+ * captures into a graph are not, and their replays must not overlap another
+ * call of the context. */
 rt_status rt_context_destroy(rt_context ctx);
 /* Sets the variant used by later trace calls on this context (see
  * rt_variant); RT_ERROR_INVALID_VALUE for unsupported values. */
@@ -510,8 +512,7 @@ rt_status rt_batch_plan_create(rt_context ctx, const rt_accel* accels, const rt_
 rt_status rt_batch_plan_create_instances(rt_context ctx, const rt_accel* accels, const rt_ray* const* rays,
                                          rt_hit* const* hits, uint32_t* const* inst_ids, const uint32_t* counts,
                                          uint32_t batch_count, rt_batch_plan* out);
-/* Enqueues the whole batch: one persistent traversal launch (after a queue
- * reset when the rays are more than the chip takes at once) and the float64
+/* Enqueues the whole batch: one persistent traversal launch and the float64
  * finalize.  The launches of a plan share its scratch: one on another stream
  * than the last waits for it.  Replays of the plan's graph, and launches that
  * the caller captures, are not ordered by the library: they must not overlap

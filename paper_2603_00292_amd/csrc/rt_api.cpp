@@ -83,9 +83,17 @@ bool valid_variant(const rt_variant& v) {
   return s_ok && wg_ok;
 }
 
-// device scratch of one launch: queue counter + global spill stack
+// Device scratch of launches one after another: queue heads and the global
+// spill stack.  The heads are three sets of kRtCounterWords.  A launch uses one
+// of the first two and zeroes the other for the next launch, so that no launch
+// depends on how the one before it ended (a kernel that zeroes them in front of
+// each launch costs it 4 us).  Captured launches, which may be replayed in any
+// number, use the third behind such a kernel.
+constexpr uint32_t kQueueSets = 3;
 struct Scratch {
-  uint32_t* counter = nullptr;   // ray queue heads (kRtCounterWords)
+  uint32_t* counter = nullptr;
+  uint32_t set = 0;              // of the next launch that is not captured
+  bool clean = false;            // that set is zero
   uint32_t* gstack = nullptr;
   size_t gstack_words = 0;
 };
@@ -224,7 +232,7 @@ uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
 
 // Makes sure scratch holds the counters and a spill stack of `words` words.
 rt_status ensure_scratch(Scratch& s, size_t words) {
-  if (!s.counter) RT_HIP(rt_malloc(&s.counter, kRtCounterWords * sizeof(uint32_t)));
+  if (!s.counter) RT_HIP(rt_malloc(&s.counter, kQueueSets * kRtCounterWords * sizeof(uint32_t)));
   if (words > s.gstack_words) {
     if (s.gstack) {
       RT_HIP(hipDeviceSynchronize());
@@ -236,6 +244,34 @@ rt_status ensure_scratch(Scratch& s, size_t words) {
     s.gstack_words = words;
   }
   return RT_SUCCESS;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return c != hipStreamCaptureStatusNone;
+}
+
+// The queue heads of a launch: `shared` ones (NULL: none), or a set of `sc`.
+// After the launch, queues_used() notes that it zeroes the next one's.
+hipError_t take_queues(Scratch& sc, uint32_t* shared, bool captured, hipStream_t s, TraceParams& p) {
+  if (p.chunk == 0u) return hipSuccess;
+  const bool next = !shared && !captured;
+  p.counter = shared ? shared : sc.counter + (captured ? 2u : sc.set) * kRtCounterWords;
+  p.clear = next ? sc.counter + (sc.set ^ 1u) * kRtCounterWords : nullptr;
+  if (next && sc.clean) {
+    sc.clean = false;
+    return hipSuccess;
+  }
+  return rtk_launch_queue_reset(p.counter, s);
+}
+void queues_used(Scratch& sc, const TraceParams& p) {
+  if (!p.clear) return;
+  sc.set ^= 1u;
+  sc.clean = true;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1203,10 +1239,10 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   LaunchShape shape = launch_shape(n, wg, resident);
   const size_t spill = rtk_spill_words(a->max_stack, v.stack_entries, any, mode);
   const bool fused = !counters && rtk_trace_fuses_finalize(any, a->two_level, mode);
-  uint32_t* counter = nullptr;
   uint32_t* gstack = nullptr;
+  uint32_t* shared = nullptr;   // queue heads shared with other contexts
   if (noalloc) {
-    // the fixed array: the queue counters, then the spill stack; the grid is
+    // the fixed array: the queue heads, then the spill stack; the grid is
     // narrowed until it fits
     uint32_t* base = noalloc_ptr(a->device);
     if (!base) return fail(RT_ERROR_HIP, "rt_trace_closest_noalloc: no scratch on device %d", a->device);
@@ -1216,16 +1252,17 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
                   "scratch", n, a->max_stack, (unsigned)RT_NOALLOC_SCRATCH_BYTES);
     const uint32_t fit = (uint32_t)std::min<size_t>(resident, (kNoAllocArray - kRtCounterWords) / (spill * wg));
     if (shape.blocks > fit) shape = launch_shape(n, wg, fit);
-    counter = base;
+    shared = base;
     gstack = base + kRtCounterWords;
   } else {
     st = ensure_scratch(ctx->scratch, spill * (size_t)shape.blocks * wg);
     if (st != RT_SUCCESS) return st;
-    counter = ctx->scratch.counter;
     gstack = ctx->scratch.gstack;
   }
   const uint32_t blocks = shape.blocks;
-  if (ctx->has_last && ctx->last_stream != s) RT_HIP(hipStreamWaitEvent(s, ctx->last_event, 0));
+  // (a capture orders only what it holds)
+  const bool captured = capturing(s);
+  if (!captured && ctx->has_last && ctx->last_stream != s) RT_HIP(hipStreamWaitEvent(s, ctx->last_event, 0));
   TraceParams p{};
   p.nodes = a->nodes;
   p.tris = a->tris;
@@ -1236,7 +1273,6 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   p.hits = hits;
   p.inst_ids = inst_ids;
   p.occluded = occ;
-  p.counter = counter;
   p.share = shape.share;
   p.chunk = shape.chunk;
   p.tile_shift = shape.tile_shift;
@@ -1258,10 +1294,11 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   }
   p.counts = counts;
   p.cap = cap;
-  if (shape.chunk != 0u) RT_HIP(rtk_launch_queue_reset(counter, s));
+  RT_HIP(take_queues(ctx->scratch, shared, captured, s, p));
   size_t tslot = ctx->tbeg.empty() ? 0 : (size_t)(ctx->trecorded % ctx->tbeg.size());
   if (!ctx->tbeg.empty()) RT_HIP(hipEventRecord(ctx->tbeg[tslot], s));
   RT_HIP(rtk_launch_trace(kern, blocks, wg, p, s));
+  queues_used(ctx->scratch, p);
   if (!ctx->tbeg.empty()) {
     RT_HIP(hipEventRecord(ctx->tend[tslot], s));
     ctx->trecorded++;
@@ -1271,9 +1308,11 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   } else if (!any && !fused) {
     RT_HIP(rtk_launch_finalize(a->two_level, 0, p, s));
   }
-  RT_HIP(hipEventRecord(ctx->last_event, s));
-  ctx->last_stream = s;
-  ctx->has_last = true;
+  if (!captured) {
+    RT_HIP(hipEventRecord(ctx->last_event, s));
+    ctx->last_stream = s;
+    ctx->has_last = true;
+  }
   return ok();
 }
 
@@ -2018,11 +2057,10 @@ rt_status rt_batch_plan_create_instances(rt_context ctx, const rt_accel* accels,
   return plan_create(ctx, accels, rays, hits, inst_ids, counts, batch_count, out);
 }
 
-static rt_status enqueue_plan(rt_batch_plan p, hipStream_t s) {
+static rt_status enqueue_plan(rt_batch_plan p, bool captured, hipStream_t s) {
   // the kernel, grid and scratch were chosen with the context's variant at
   // creation; a later rt_context_set_variant does not change the plan
   TraceParams q{};
-  q.counter = p->scratch.counter;
   q.share = p->shape.share;
   q.chunk = p->shape.chunk;
   q.tile_shift = p->shape.tile_shift;
@@ -2036,8 +2074,9 @@ static rt_status enqueue_plan(rt_batch_plan p, hipStream_t s) {
   q.refill_min = p->ctx->refill_min;
   q.status = p->ctx->status;
   q.root = RT_CHILD_EMPTY;
-  if (p->shape.chunk != 0u) RT_HIP(rtk_launch_queue_reset(p->scratch.counter, s));
+  RT_HIP(take_queues(p->scratch, nullptr, captured, s, q));
   RT_HIP(rtk_launch_trace(p->kernel, p->shape.blocks, p->workgroup, q, s));
+  queues_used(p->scratch, q);
   RT_HIP(rtk_launch_finalize(p->two_level, 1, q, s));
   return RT_SUCCESS;
 }
@@ -2053,13 +2092,11 @@ rt_status rt_batch_plan_launch(rt_batch_plan plan, void* stream) {
   if (st != RT_SUCCESS) return st;
   // the plan's launches share its scratch: on another stream than the last
   // one, this launch waits for it (a capture orders only what it holds)
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-  const bool ordered = capture == hipStreamCaptureStatusNone;
-  if (ordered && plan->has_last && plan->last_stream != s) RT_HIP(hipStreamWaitEvent(s, plan->last_event, 0));
-  st = enqueue_plan(plan, s);
+  const bool captured = capturing(s);
+  if (!captured && plan->has_last && plan->last_stream != s) RT_HIP(hipStreamWaitEvent(s, plan->last_event, 0));
+  st = enqueue_plan(plan, captured, s);
   if (st != RT_SUCCESS) return st;
-  if (ordered) {
+  if (!captured) {
     RT_HIP(hipEventRecord(plan->last_event, s));
     plan->last_stream = s;
     plan->has_last = true;
@@ -2076,7 +2113,7 @@ rt_status rt_batch_plan_graph(rt_batch_plan plan, void* stream, void** out_graph
   if (!plan->graph_exec) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     RT_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    rt_status e = (plan->total > 0) ? enqueue_plan(plan, s) : RT_SUCCESS;
+    rt_status e = (plan->total > 0) ? enqueue_plan(plan, true, s) : RT_SUCCESS;
     hipGraph_t g = nullptr;
     hipError_t ee = hipStreamEndCapture(s, &g);
     if (e != RT_SUCCESS) {

@@ -34,9 +34,10 @@ struct TraceParams {
   uint32_t* inst_ids;
   uint8_t* occluded;
   // See LaunchShape; counter[v * kRtQueueStride] counts the rays of queue v's
-  // chunks given out, and carries kRtQueuesDone (rtk_launch_queue_reset zeroes
-  // the heads before the launch).
+  // chunks given out, and carries kRtQueuesDone.  Zero before the launch, which
+  // zeroes the heads at `clear` (NULL: none) for another one.
   uint32_t* counter;
+  uint32_t* clear;
   uint32_t share, chunk, tile_shift;
   uint32_t* gstack;      // global stack: per thread of the grid, the entries past the LDS ones
   const BatchDesc* batches;

@@ -569,6 +569,7 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   st.cap = P.max_stack;
   st.init(tid);
   if (tid == 0) lds_empty = 0;
+  if (P.clear && blockIdx.x == 0 && tid < kRtQueues) P.clear[tid * kRtQueueStride] = 0u;
   const uint32_t n_top = min((uint32_t)kTop, P.top_nodes);
   if constexpr (kTop > 0) {
     const float4* src = reinterpret_cast<const float4*>(P.nodes);

@@ -80,6 +80,35 @@ def test_context_on_several_streams(gpu):
         assert torch.equal(h.view(torch.int32), ref[:n]), n
 
 
+def test_captured_between_eager(gpu):
+    """Closest and any hits captured into a caller's graph, replayed between
+    launches on other streams: every replay and every launch is whole."""
+    torch, api, ctx, W, acc, rays, ref = gpu
+    occ = api.trace_any(acc, rays)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        hits, _ = api.trace_closest(acc, rays)
+        any_hit = api.trace_any(acc, rays)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for rep in range(5):
+        hits.fill_(-1.0)
+        any_hit.fill_(7)
+        torch.cuda.synchronize()
+        g.replay()
+        if rep % 2:
+            g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(hits.view(torch.int32), ref) and torch.equal(any_hit, occ), rep
+        outs = []
+        for s in streams[: 1 + rep % 2]:
+            with torch.cuda.stream(s):
+                outs.append(api.trace_closest(acc, rays)[0])
+        torch.cuda.synchronize()
+        for h in outs:
+            assert torch.equal(h.view(torch.int32), ref), rep
+
+
 def test_process_wide_scratch(gpu):
     """Contexts of different variants, so of different grids, one after another."""
     torch, api, ctx, W, acc, rays, ref = gpu
