@@ -122,6 +122,7 @@ struct AoParams {
   uint32_t samples;
   double offset;
   float radius;
+  uint32_t block;        // samples of a workgroup (set by the launch)
 };
 
 // Kernel handle for a variant (mode 0: one accel, mode 1: batched closest,

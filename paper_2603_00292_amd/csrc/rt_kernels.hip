@@ -1520,7 +1520,7 @@ __global__ __launch_bounds__(256) void refit_nodes_kernel(float* nodes, const rt
 //
 // The frame takes more float64 work than a sample (two dependent fetches, two
 // square roots, six divisions against one of each kind and a sine), so a
-// workgroup forms the frames of its kAoSamples samples' rays in LDS first,
+// workgroup forms the frames of its samples' rays in LDS first,
 // one a thread, and each thread then takes its samples.  Bound by float64
 // issue (about 500 instructions a sample) when every sample formed its own
 // frame and took sine and cosine apart; now by its 40 bytes of HBM a sample:
@@ -1593,14 +1593,12 @@ __device__ __forceinline__ AoFrame ao_frame(const AoParams& P, uint32_t ray) {
   return F;
 }
 
-// samples per workgroup; LDS holds the frames of (kAoSamples - 1) / samples + 2
-// rays (a workgroup's samples may begin and end inside a ray's)
-constexpr uint32_t kAoSamples = 512;
-
+// LDS holds the frames of (block - 1) / samples + 2 rays (a workgroup's samples
+// may begin and end inside a ray's).
 __global__ __launch_bounds__(256) void ao_rays_kernel(AoParams P) {
   extern __shared__ AoFrame frames[];
   const uint32_t total = P.n * P.samples;
-  const uint32_t i0 = blockIdx.x * kAoSamples, i1 = min(total, i0 + kAoSamples);
+  const uint32_t i0 = blockIdx.x * P.block, i1 = min(total, i0 + P.block);
   const uint32_t ray0 = i0 / P.samples, ray1 = (i1 - 1u) / P.samples;
   for (uint32_t k = threadIdx.x; k <= ray1 - ray0; k += 256) frames[k] = ao_frame(P, ray0 + k);
   __syncthreads();
@@ -1825,10 +1823,15 @@ hipError_t rtk_launch_ao_rays(const AoParams& p, hipStream_t stream) {
   uint64_t total = (uint64_t)p.n * p.samples;
   if (total == 0) return hipSuccess;
   AoParams q = p;
+  // 512 samples to a workgroup, so that its threads share frames; one sample a
+  // ray shares none, and 256 leave room for seven workgroups on a CU instead of
+  // three (1,000,003 rays, 512 / 256: one sample 49.8 / 48.3 us, on 1,024
+  // instances 33.9 / 32.1; two samples 55.9 / 55.8 and 37.8 / 40.3)
+  q.block = p.samples == 1u ? 256u : 512u;
   void* args[] = {&q};
   return hipLaunchKernel(reinterpret_cast<const void*>(&rtk::ao_rays_kernel),
-                         dim3((uint32_t)((total + rtk::kAoSamples - 1) / rtk::kAoSamples)), dim3(256), args,
-                         ((rtk::kAoSamples - 1) / p.samples + 2) * sizeof(rtk::AoFrame), stream);
+                         dim3((uint32_t)((total + q.block - 1) / q.block)), dim3(256), args,
+                         ((q.block - 1) / p.samples + 2) * sizeof(rtk::AoFrame), stream);
 }
 
 hipError_t rtk_launch_ao_resolve(const uint8_t* occluded, uint32_t n, uint32_t samples, float* ao,
