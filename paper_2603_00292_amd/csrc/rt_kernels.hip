@@ -569,7 +569,6 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   st.cap = P.max_stack;
   st.init(tid);
   if (tid == 0) lds_empty = 0;
-  if (P.clear && blockIdx.x == 0 && tid < kRtQueues) P.clear[tid * kRtQueueStride] = 0u;
   const uint32_t n_top = min((uint32_t)kTop, P.top_nodes);
   if constexpr (kTop > 0) {
     const float4* src = reinterpret_cast<const float4*>(P.nodes);
@@ -902,6 +901,8 @@ __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
       }
     }
   }
+  // (at the end: the start is what launches of few rays wait for)
+  if (P.clear && blockIdx.x == 0 && tid < kRtQueues) P.clear[tid * kRtQueueStride] = 0u;
   if constexpr (COUNT) {
     if (st.over) __hip_atomic_store(P.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
