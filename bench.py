@@ -340,7 +340,7 @@ def main():
                    "variant": list(ctx.variant), "autotuned": tuned is not None,
                    "autotune_cached": bool(tuned is not None and cached), "query": "closest",
                    "inputs_sha256": W.checksum()[:16]},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "memory", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "kernel": "trace_kernel<%d, %d, %d> closest-hit traversal + float64 finalize" % (
                          info["node_width"], ctx.variant[0], ctx.variant[1]),
@@ -350,9 +350,9 @@ def main():
                      "frac_with_finalize": round(achieved_with_finalize / HBM_PEAK_GBS, 4),
                      "traffic_frac": None if traffic is None else round(
                          traffic / (mean_kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                     "limiter": "L1 accesses (a divergent 16-byte load takes a CU one cycle per lane): "
-                                "the measured HBM traffic is below the algorithmic bytes, most "
-                                "fetches hit the caches",
+                     "limiter": "the path through L1 and L2: most fetches hit the caches, so achieved "
+                                "(algorithmic bytes) may pass the HBM peak; traffic_frac is the HBM side, "
+                                "and the L1's data return is busy 93% of the cycles, its address unit 68%",
                      "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4),
                      "valu": None if valu is None else {
                          "bound": "alu", "wave_instructions": valu[0],

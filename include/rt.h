@@ -136,10 +136,15 @@ typedef struct rt_build_options {
 } rt_build_options;
 
 /* Trace variant (launch configuration of the traversal kernels):
- * stack_entries = per-lane traversal stack kept in LDS (8, 16, 32; deeper
- * entries spill to a global stack), workgroup = threads per workgroup (64,
- * 128, 256).  The defaults are 16 and 256.  Results do not depend on the
- * variant (§7.5 notes that stack and block sizes are compile-time choices). */
+ * stack_entries = size of the per-lane traversal stack kept in LDS (8, 16,
+ * 32: that many entries for any-hit and all-hit queries, and 8, 10, 13 for
+ * closest hits, whose entries are twice as large; deeper ones spill to a
+ * global stack), workgroup = threads per workgroup (64, 128, 256).  The
+ * defaults are 16 and 256.  Results do not depend on the variant (§7.5 notes
+ * that stack and block sizes are compile-time choices).  Accels of more than
+ * 4 GiB of nodes, and all accels of a context created with the environment
+ * variable RT_WIDE_NODES=1, are traced with 64-bit node addresses, which
+ * exist for 16 and 256 only: whatever the context's variant, they run that. */
 typedef struct rt_variant {
   uint32_t stack_entries;
   uint32_t workgroup;
@@ -171,8 +176,9 @@ typedef struct rt_accel_info {
  * allocated, and objects it was to create are not created.  Unset or 0:
  * no failure (this call disarms an earlier one). */
 rt_status rt_context_create(int hip_device, rt_context* out);
-/* Frees the context's scratch (global stacks, queue heads).  An accel keeps the context it was built with and traces with that context's
- * variant and scratch, so destroy every accel and batch plan of a context
+/* Frees the context's scratch (global stacks, queue heads).  An accel keeps
+ * the context it was built with and traces with that context's variant and
+ * scratch, so destroy every accel and batch plan of a context
  * before the context.  Trace calls of one context on different streams are
  * ordered one after another (they share the scratch); calls that the caller
  * captures into a graph are not, and their replays must not overlap another
@@ -462,12 +468,12 @@ rt_status rt_trace_counters(rt_accel accel, const rt_ray* rays, uint32_t n, int 
 
 /* rt_trace_counters with n_counters (4 or 8) uint64 counters.  With 8 the
  * call also ADDS the counting kernel's wave-level loop counts to
- * counters[4..7]: passes of its outer loop (refill check, node phase, leaf
- * phase), refills, node-loop iterations and leaf-loop iterations, every
- * iteration of a wave counted once.  A wave iteration issues its
- * instructions for all 64 lanes, so node visits / (64 x node-loop
- * iterations) is the node phase's lane occupancy, triangle tests / (64 x
- * leaf-loop iterations) the leaf phase's.  A diagnostic of how the work of
+ * counters[4..7]: passes of its outer loop (refill check, then a run of steps
+ * of one kind), refills, node-visit steps and triangle-test steps, every
+ * step of a wave counted once.  A step issues its instructions for all 64
+ * lanes, so node visits / (64 x node-visit steps) is the lane occupancy of
+ * node visits, triangle tests / (64 x triangle-test steps) that of triangle
+ * tests.  A diagnostic of how the work of
  * §7.5's stack traversal spreads over the lanes of a wave.
  * Errors: as rt_trace_counters; RT_ERROR_INVALID_VALUE for another
  * n_counters. */

@@ -214,11 +214,17 @@ void destroy_accel(rt_accel_s* a) {
 }
 
 // Workgroups of a traversal kernel that a launch runs at once: those that fit,
-// up to 20 waves per CU.  The kernel is bound by the CU's L1 (a divergent
-// 16-byte load takes it a cycle per lane), and more rays in flight than that
-// crowd it: on 4M incoherent rays 4 / 5 / 6 / 7 workgroups of four waves took
-// 1,449 / 1,424 / 1,473 / 1,557 us, ambient occlusion 1,780 / 1,647 / 1,637 /
-// 1,758 us, 1,024 instances 3,069 / 2,760 / 2,858 / - us.
+// up to 20 waves per CU.  The kernel keeps the CU's L1 busy (on 4M incoherent
+// rays its address unit 68% of the cycles, its data return 93%; 35% wait for a
+// line already on its way), and more rays in flight than that crowd it: 4 / 5 /
+// 6 / 7 workgroups of four waves took 1,449 / 1,424 / 1,473 / 1,557 us, ambient
+// occlusion 1,780 / 1,647 / 1,637 / 1,758, 1,024 instances 3,069 / 2,760 /
+// 2,858 / -.  The other queries, 1,000,003 rays, 4-wide nodes, 4 / 5 / 6: any
+// hit 324 / 321 / 366, with options 484 / 466 / 523, plans of 8,192 rays 521 /
+// 491 / 541, instances 492 / 472 / 498, any hit 368 / 364 / 396; lists of eight
+// (250,007 rays) 971 / 959 / 1,376, on instances 845 / 870 / 1,128.  2-wide
+// nodes: 587 / 599 / 622, on instances 561 / 535 / 572, any hit 435 / 429 /
+// 402.  Of 8-wide ones four fit (504, on instances 526).
 uint32_t resident_blocks(const void* kern, int wg, int cu_count) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, wg, 0) != hipSuccess ||
@@ -1277,7 +1283,11 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   p.chunk = shape.chunk;
   p.tile_shift = shape.tile_shift;
   p.gstack = gstack;
-  // (a launch of few rays does not earn the copy: 64 rays 27.1 against 26.5 us)
+  // A launch of few rays does not earn the copy.  Without / with it, closest
+  // hits on 1,310,720 triangles: 20,011 rays 154.5 / 158.5 us, 30,011 163.9 /
+  // 164.2, 60,013 166.3 / 166.4, 100,003 180.5 / 178.3, 200,003 191.1 / 188.0,
+  // 327,680 232.7 / 222.5; on 1,024 instances 20,011 121.1 / 122.3, 60,013
+  // 146.7 / 147.0, 200,003 211.5 / 208.6.
   p.top_nodes = n < 32768u ? 0u : a->info.node_count;
   p.root = a->root;
   p.n = n;

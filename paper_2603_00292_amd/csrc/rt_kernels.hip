@@ -79,10 +79,10 @@ __device__ __forceinline__ rt_ray load_ray(const rt_ray* rays, uint32_t i) {
 // found since it was pushed is dropped when it is popped, without a fetch.
 // Slot 0 of a lane's LDS column holds a sentinel (RT_CHILD_EMPTY at distance
 // -inf), so a pop needs no check for an empty stack.  Entry i lives in LDS
-// slot i + 1 while i < D, and at gstack[(i - D) * gstride + thread] beyond: D
-// covers all but some 0.5% of the pushes of the incoherent workloads.
-// A push beyond `cap` (the builder's bound on the entries a ray can need,
-// which the global stack is sized for; never below D) is not stored.  The
+// slot i + 1 while i < D, and at gstack[(i - D) * gstride + thread] beyond (D =
+// 10, 4,194,304 incoherent rays: 0.11 entries a ray, of 16.9 node visits).
+// A push beyond both D and `cap` (the builder's bound on the entries a ray can
+// need, which the global stack is sized for) is not stored.  The
 // counting variant (CHECK) also remembers it and raises the launch's
 // host-mapped status word at the end, which the host turns into an error on
 // the context's next call, and records the deepest fill.  The query kernels
@@ -98,7 +98,7 @@ struct Stack {
   char* lds;           // the workgroup's array
   uint32_t* glob;      // this lane's column: glob[i * gstride] (references; a popped one is not culled)
   uint32_t gstride;
-  uint32_t cap;        // entries this lane may hold (at least D)
+  uint32_t cap;        // entries this lane may hold (the D of LDS in any case)
   uint32_t off;        // byte offset in lds of the slot the next push takes
   uint32_t peak;       // CHECK: the most entries held
   uint32_t spills;     // CHECK: entries stored in global memory
@@ -192,9 +192,10 @@ __device__ __forceinline__ double raw_max(double a, double b) {
 
 // W-wide node visit: (entry distance, child reference) of the children that
 // the ray enters, nearest first; the others follow with distance +inf.
-// A divergent 16-byte load costs the CU's address unit one cycle per lane, so
-// a 4-wide visit costs 7 cycles per lane there and its box tests about twice
-// that in VALU issue; both are kept low:
+// A divergent 16-byte load costs the CU's address unit about one cycle per lane
+// (4,194,304 incoherent rays: busy 68% of the cycles, the data return behind it
+// 93%), so a 4-wide visit costs 7 cycles per lane there and its box tests about
+// twice that in VALU issue; both are kept low:
 // OFF32 (nodes of one accel in less than 4 GiB): 32-bit byte offsets from the
 // uniform node pointer, and each lane loads its near and far planes at
 // offsets chosen by the sign of its direction instead of loading both in
@@ -203,8 +204,8 @@ __device__ __forceinline__ double raw_max(double a, double b) {
 // (batched plans) select after the load.
 // TOP: nodes [0, n_top), the upper levels of the tree, are read from a copy
 // in LDS (kNodeParts 16-byte parts each, the pad left out: the odd stride
-// spreads the parts of different nodes over the banks), which takes 28% of
-// the L1 accesses off 16.8M ambient-occlusion rays (1,650 -> 1,570 us; camera
+// spreads the parts of different nodes over the banks), which takes their
+// accesses off the L1 (16.8M ambient-occlusion rays 1,650 -> 1,570 us; camera
 // and shadow rays 1,652 -> 1,626, 300,007 visibility rays 137 -> 133, 1,024
 // instances 2,773 -> 2,725, incoherent rays 1,427 -> 1,413).
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -533,8 +534,9 @@ __device__ __forceinline__ void finalize_index(const TraceParams& P, uint32_t i)
 // entry and exit.  A lane with a leaf in hand keeps traversing until it meets
 // a second one or a frame change, so it can serve either step.  Running each
 // phase until no lane of the wave had work left in it, as before, left 36% of
-// the lanes busy in node visits and 29% in triangle tests on incoherent rays;
-// choosing step by step leaves about 65% and 33%.
+// the lanes busy in node visits and 29% in triangle tests on incoherent rays,
+// with 19.2 visits and 12.5 tests a ray; choosing step by step leaves 57% and
+// 28% (the counting variant's figures), with 16.9 and 11.1.
 template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool OFF32, bool COUNT = false>
 __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   constexpr bool CULL = !ANY && MODE != 3;

@@ -32,7 +32,12 @@ struct LaunchShape {
 // share, and the queues are not used.  Few rays are spread over the chip's
 // 1,024 SIMDs first (64 rays on a 20,480-triangle mesh: 26 us a call with one
 // ray a wave, 35 with 32), then 32 to a wave (65,536 rays: 49 us; 16 to a
-// wave 58).  Beyond, waves take a chunk each and then more from the queues: 64
+// wave 58).  On either side of 64 the better way depends on the rays: one share
+// a wave / queues, 250,007 rays on 1,310,720 triangles 211 / 237 us, on 1,024
+// instances 227 / 228; 327,681 rays 229 / 226, instances 246 / 230, but 120 /
+// 164 on 20,480 triangles; 500,009 rays 293 / 318, 295 / 301 and 129 / 143.  A
+// long share can leave its costly rays to one wave, which queues do not.
+// Beyond, waves take a chunk each and then more from the queues: 64
 // rays, or more when the average wave would need more than a quarter of its
 // kRtRangesPerWave ranges (the waves together can then hold four times the
 // rays, so a wave with a full list always leaves the rest to others).  A queue
