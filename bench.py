@@ -352,7 +352,7 @@ def main():
                          traffic / (mean_kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "limiter": "the path through L1 and L2: most fetches hit the caches, so achieved "
                                 "(algorithmic bytes) may pass the HBM peak; traffic_frac is the HBM side, "
-                                "and the L1's data return is busy 93% of the cycles, its address unit 68%",
+                                "and the L1's data return is busy 95% of the cycles, its address unit 68%",
                      "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4),
                      "valu": None if valu is None else {
                          "bound": "alu", "wave_instructions": valu[0],

@@ -137,9 +137,9 @@ typedef struct rt_build_options {
 
 /* Trace variant (launch configuration of the traversal kernels):
  * stack_entries = size of the per-lane traversal stack kept in LDS (8, 16,
- * 32: that many entries for any-hit and all-hit queries, and 8, 10, 13 for
- * closest hits, whose entries are twice as large; deeper ones spill to a
- * global stack), workgroup = threads per workgroup (64, 128, 256).  The
+ * 32: that many entries for any-hit queries, 16 instead of 32 at node widths
+ * 4 and 8, and 8, 10, 13 for closest hits, whose entries are twice as large;
+ * deeper ones spill to a global stack), workgroup = threads per workgroup (64, 128, 256).  The
  * defaults are 16 and 256.  Results do not depend on the variant (§7.5 notes
  * that stack and block sizes are compile-time choices).  Accels of more than
  * 4 GiB of nodes, and all accels of a context created with the environment

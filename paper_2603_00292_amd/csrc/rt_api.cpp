@@ -215,7 +215,7 @@ void destroy_accel(rt_accel_s* a) {
 
 // Workgroups of a traversal kernel that a launch runs at once: those that fit,
 // up to 20 waves per CU.  The kernel keeps the CU's L1 busy (on 4M incoherent
-// rays its address unit 68% of the cycles, its data return 93%; 35% wait for a
+// rays its address unit 68% of the cycles, its data return 95%; 35% wait for a
 // line already on its way), and more rays in flight than that crowd it: 4 / 5 /
 // 6 / 7 workgroups of four waves took 1,449 / 1,424 / 1,473 / 1,557 us, ambient
 // occlusion 1,780 / 1,647 / 1,637 / 1,758, 1,024 instances 3,069 / 2,760 /
@@ -1243,7 +1243,7 @@ static rt_status launch_trace(rt_accel a, const rt_ray* rays, uint32_t n, rt_hit
   uint32_t wg = v.workgroup;
   uint32_t resident = noalloc ? peek_resident(ctx, kern, (int)wg) : cached_resident(ctx, kern, (int)wg);
   LaunchShape shape = launch_shape(n, wg, resident);
-  const size_t spill = rtk_spill_words(a->max_stack, v.stack_entries, any, mode);
+  const size_t spill = rtk_spill_words(a->max_stack, v.stack_entries, any, mode, a->width);
   const bool fused = !counters && rtk_trace_fuses_finalize(any, a->two_level, mode);
   uint32_t* gstack = nullptr;
   uint32_t* shared = nullptr;   // queue heads shared with other contexts
@@ -2041,7 +2041,7 @@ static rt_status plan_create(rt_context ctx, const rt_accel* accels, const rt_ra
   p->shape = launch_shape(p->total, wg, resident);
   p->workgroup = wg;
   p->stack_entries = v.stack_entries;
-  const size_t spill = rtk_spill_words(max_stack, v.stack_entries, false, 1);
+  const size_t spill = rtk_spill_words(max_stack, v.stack_entries, false, 1, width);
   hipError_t e1 = rt_malloc(&p->descs, d.size() * sizeof(BatchDesc));
   hipError_t e2 = rt_malloc(&p->offsets, off.size() * sizeof(uint32_t));
   if (e1 != hipSuccess || e2 != hipSuccess)

@@ -194,7 +194,7 @@ __device__ __forceinline__ double raw_max(double a, double b) {
 // the ray enters, nearest first; the others follow with distance +inf.
 // A divergent 16-byte load costs the CU's address unit about one cycle per lane
 // (4,194,304 incoherent rays: busy 68% of the cycles, the data return behind it
-// 93%), so a 4-wide visit costs 7 cycles per lane there and its box tests about
+// 95%), so a 4-wide visit costs 7 cycles per lane there and its box tests about
 // twice that in VALU issue; both are kept low:
 // OFF32 (nodes of one accel in less than 4 GiB): 32-bit byte offsets from the
 // uniform node pointer, and each lane loads its near and far planes at
@@ -540,7 +540,7 @@ __device__ __forceinline__ void finalize_index(const TraceParams& P, uint32_t i)
 template <int W, int S, int WG, bool ANY, bool INST, int MODE, bool OFF32, bool COUNT = false>
 __global__ __launch_bounds__(WG) void trace_kernel(TraceParams P) {
   constexpr bool CULL = !ANY && MODE != 3;
-  constexpr int D = rtk_lds_entries(S, CULL);
+  constexpr int D = rtk_lds_entries(S, CULL, W);
   using Stk = Stack<D, WG, CULL, COUNT>;
   using E = typename Stk::E;
   __shared__ __align__(8) char lds_stack[Stk::kLdsEnd];
@@ -1672,7 +1672,8 @@ const void* count_kernel_w(bool any, bool inst) {
 template <int W, int S, int WG, int MODE, bool OFF32>
 const void* pick_any(bool any, bool inst) {
   if constexpr (MODE != 3) {
-    if (any) return inst ? kernel_ptr<W, S, WG, true, true, MODE, OFF32>() : kernel_ptr<W, S, WG, true, false, MODE, OFF32>();
+    constexpr int A = rtk_lds_entries(S, false, W);  // any-hit variants of one LDS stack are one kernel
+    if (any) return inst ? kernel_ptr<W, A, WG, true, true, MODE, OFF32>() : kernel_ptr<W, A, WG, true, false, MODE, OFF32>();
   }
   return inst ? kernel_ptr<W, S, WG, false, true, MODE, OFF32>() : kernel_ptr<W, S, WG, false, false, MODE, OFF32>();
 }

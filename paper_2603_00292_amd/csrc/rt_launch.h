@@ -88,14 +88,18 @@ constexpr uint32_t rt_first_ray(uint32_t block, uint32_t wave, uint32_t blocks, 
 // references for any-hit and all-hit queries; closest hits keep 8-byte
 // (distance, reference) entries, and as many as leave a CU's LDS to 20 waves:
 // 8, 10 and 13.  (With 5 of the 8, 2-wide nodes spilled more than the cull
-// saved: 400,003 incoherent rays 480 us against 437, workgroups of 64.)
-constexpr int rtk_lds_entries(int stack, bool cull) {
-  return !cull || stack <= 8 ? stack : stack <= 16 ? 10 : 13;
+// saved: 400,003 incoherent rays 480 us against 437, workgroups of 64.)  Of 32
+// references 16 lie in LDS where the upper tree levels can use the rest (any
+// hit of 2,000,003 incoherent rays, workgroups of 256, 32 / 16: 4-wide nodes
+// 580 / 512 us, 8-wide 700 / 585, but 2-wide, which have no such copy, 716 /
+// 739).
+constexpr int rtk_lds_entries(int stack, bool cull, int width) {
+  return stack <= 8 ? stack : cull ? (stack <= 16 ? 10 : 13) : (width >= 4 ? 16 : stack);
 }
 constexpr bool rtk_stack_culls(bool any, int mode) { return !any && mode != 3; }
 // global stack words per thread (4-byte references) for a bound of max_stack entries
-constexpr size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode) {
-  const uint32_t lds = (uint32_t)rtk_lds_entries((int)stack, rtk_stack_culls(any, mode));
+constexpr size_t rtk_spill_words(uint32_t max_stack, uint32_t stack, bool any, int mode, int width) {
+  const uint32_t lds = (uint32_t)rtk_lds_entries((int)stack, rtk_stack_culls(any, mode), width);
   return max_stack > lds ? max_stack - lds : 1u;
 }
 
@@ -131,5 +135,5 @@ constexpr size_t rtk_noalloc_budget(uint32_t n, uint32_t refill_min, uint32_t st
 // than the variant's entries in LDS, 19 fewer of 32, so that the deepest stack
 // taken needs this much more (256 threads).
 constexpr size_t rtk_noalloc_array(size_t words) {
-  return words + kRtCounterWords + (32u - (uint32_t)rtk_lds_entries(32, true)) * 256u;
+  return words + kRtCounterWords + (32u - (uint32_t)rtk_lds_entries(32, true, 4)) * 256u;
 }

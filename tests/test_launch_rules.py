@@ -36,7 +36,7 @@ int main() {
           for (uint32_t bound = 1; bound < 300000; ++bound) {
             if (rtk_noalloc_budget(n, refill, s, wg, bound) > limit) break;
             ++taken;
-            if (kRtCounterWords + rtk_spill_words(bound, s, false, 0) * wg > array) {
+            if (kRtCounterWords + rtk_spill_words(bound, s, false, 0, 4) * wg > array) {
               std::printf("stack %u workgroup %u rays %u bound %u\n", s, wg, n, bound);
               ++failures;
             }
@@ -189,12 +189,17 @@ int main() {
       ++failures;
     }
   }
-  // the closest-hit stacks (and the sentinel entry) of every variant
+  // the stacks (and the sentinel entry) of every variant
   for (uint32_t wg : {64u, 128u, 256u})
     for (int stack : {8, 16, 32}) {
-      const uint32_t bytes = (uint32_t)(rtk_lds_entries(stack, true) + 1) * 8u * wg + 4u;
+      const uint32_t bytes = (uint32_t)(rtk_lds_entries(stack, true, 4) + 1) * 8u * wg + 4u;
       if (rtk_lds_blocks(bytes) * (wg / 64u) < (uint32_t)kRtWavesPerCu) {
         std::printf("stack %d workgroup %u: %u waves\n", stack, wg, rtk_lds_blocks(bytes) * (wg / 64u));
+        ++failures;
+      }
+      const uint32_t refs = (uint32_t)(rtk_lds_entries(stack, false, 4) + 1) * 4u * wg + 4u;
+      if (rtk_lds_blocks(refs) * (wg / 64u) < (uint32_t)kRtWavesPerCu) {
+        std::printf("any hit, stack %d workgroup %u: %u waves\n", stack, wg, rtk_lds_blocks(refs) * (wg / 64u));
         ++failures;
       }
       // the upper levels fill what is left, and no more
@@ -213,6 +218,6 @@ int main() {
 
 
 def test_resident_waves(tmp_path):
-    """Workgroups that a CU's LDS holds, and the closest-hit stacks of all
-    variants at the number of waves that a launch is made for."""
+    """Workgroups that a CU's LDS holds, and the stacks of all variants at the
+    number of waves that a launch is made for."""
     run_driver(tmp_path, RESIDENT)
